@@ -106,6 +106,19 @@ __device__ __forceinline__ bool region_has(const Region &R, const PatternArgs &P
   return r >= R.lo && r <= R.hi && c >= R.clo && c <= R.chi;
 }
 
+// Whether region R may hold any of the positions [y0, y0 + len) (y0, len
+// wave-uniform). Exact for the 1-D patterns and for runs inside one grid row; a
+// run over several rows is tested by its rows only (never false for a run that
+// holds an allowed position).
+__device__ __forceinline__ bool region_meets(const Region &R, const PatternArgs &P, int y0, int len) {
+  const int y1 = y0 + len - 1;
+  if (R.one_d) return R.lo <= y1 && R.hi >= y0;
+  const int r0 = (int)fdiv((uint32_t)y0, P.wdiv), r1 = (int)fdiv((uint32_t)y1, P.wdiv);
+  const bool rows = R.lo <= r1 && R.hi >= r0;
+  if (r0 != r1) return rows;
+  return rows && R.clo <= y1 - r0 * P.W && R.chi >= y0 - r0 * P.W;
+}
+
 // Element mask over NB 32x32 accumulator blocks. Slot v of this lane in block
 // kb holds the position base + 32*kb + 16*(v/8) + v%8 (runs of eight
 // consecutive positions; base = first position of block 0 + 8 * lane half).
@@ -193,6 +206,74 @@ __device__ __forceinline__ int row_perm(int i) {
   // accumulator row i = 8a + 4g + b  ->  operand row 16(a/2) + 8g + 4(a%2) + b
   const int a = i >> 3, g = (i >> 2) & 1, b = i & 3;
   return 16 * (a >> 1) + 8 * g + 4 * (a & 1) + b;
+}
+
+// ---------------------------------------------------------------------------
+// fp32 matrix products over a 32-row block of a row tile in LDS
+// (v_mfma_f32_32x32x2_f32: lane (l % 32, half = l / 32) gives A's row l % 32 and B's
+// column l % 32, at contraction index `half`; accumulators as above). The LDS
+// reads of one group of eight products are issued before the products of the
+// group in front of it (512 cycles): left alone, the compiler reads each operand
+// right before its use into the same registers and waits for every read. At
+// d = 64 and 128-row tiles the forced order is 5-7% faster (fwd on 32 x 4096 rows,
+// band of half-width 128: 118.6 -> 110.9 us); at d = 32, with twice the waves
+// per SIMD, it is 2% slower, so there the order is left to the compiler.
+
+// acc += rows . b: A = the block's rows, this lane's row in 16-byte chunks at
+// blk + addr[c]; b the other operand's chunks. NC chunks of four contraction steps.
+template <int NC>
+__device__ __forceinline__ void mfma_rows_f32(const char *blk, const int (&addr)[NC], const f32x4 (&b)[NC],
+                                              f32x16 &acc) {
+  f32x4 x[2][2];
+  auto load = [&](int g) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) x[g & 1][e] = *reinterpret_cast<const f32x4 *>(blk + addr[2 * g + e]);
+  };
+  load(0);
+#pragma unroll
+  for (int g = 0; g < NC / 2; ++g) {
+    if (g + 1 < NC / 2) load(g + 1);
+    if constexpr (NC == 8) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g & 1][e][i], b[2 * g + e][i], acc, 0, 0, 0);
+  }
+}
+
+// acc += columns . w: w holds one value per row of the block in accumulator layout
+// (slot t of lane half h: row 16 (t/8) + 8 h + t % 8), and at(t) is the LDS address
+// of this lane's column (NDB = 1) or pair of columns (NDB = 2, one accumulator
+// each) in slot t's row.
+template <int NDB, class At>
+__device__ __forceinline__ void mfma_cols_f32(At at, const f32x16 &w, f32x16 (&acc)[NDB]) {
+  constexpr int PER = 8 / NDB, NG = 16 / PER;   // slots per group, groups
+  float x[2][PER][NDB];
+  auto load = [&](int g) {
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const char *p = at(PER * g + e);
+      if constexpr (NDB == 2) {
+        const float2 t = *reinterpret_cast<const float2 *>(p);
+        x[g & 1][e][0] = t.x;
+        x[g & 1][e][1] = t.y;
+      } else {
+        x[g & 1][e][0] = *reinterpret_cast<const float *>(p);
+      }
+    }
+  };
+  load(0);
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    if (g + 1 < NG) load(g + 1);
+    if constexpr (NDB == 2) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < PER; ++e)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        acc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g & 1][e][db], w[PER * g + e], acc[db], 0, 0, 0);
+  }
 }
 
 // LDS byte address of a pointer into __shared__ memory.
