@@ -7,11 +7,14 @@
 //
 // What bounds it: the matrix cores. A wave owns 32 queries and takes a key tile
 // in two blocks of 32 keys; a block is D/2 + D/2 products of 64 cycles (4096
-// at d = 64) beside about 900 cycles of softmax. The operands come from LDS at
+// at d = 64) beside about 600 cycles of softmax. The operands come from LDS at
 // one 16-byte read per four products (K) and one 8-byte read per two (V), far
-// below the LDS rate. (Plain FMAs with four lanes per row read every K and V
-// element from LDS once per 16 FMAs and ran at 24 TFLOP/s of tile products on
-// the 64x64 band at d = 64: 128 us; this kernel: see the measured line below.)
+// below the LDS rate. The softmax's vector work does not hide behind fp32 matrix
+// products (measured: 16 FMAs beside 8 products, of any wave of the SIMD, add
+// their whole issue time), so 80% of the matrix rate is about the limit. Measured
+// against plain FMAs with four lanes per row, which read every K and V element
+// from LDS once per 16 FMAs: band of half-width 128 on 64x64 at d = 64, 8 heads
+// 128 -> 36 us, 32 heads 293 -> 111 us (113 TFLOP/s over the listed tiles).
 //
 //   S^T = K Q^T     A = K rows from LDS, B = the wave's q in registers. Lane half
 //                   h contracts d in [h D/2, (h+1) D/2), so a lane reads its part
