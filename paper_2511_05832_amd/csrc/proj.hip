@@ -7,28 +7,13 @@
 //         q / k / v [B, heads, N, d] by f -> (which, head, e)
 //   out:  y[t, f] = sum_k o[b, k/d, n, k%d] W[f, k]  (heads merged on the fly)
 //
-// MFMA D = A B with A = a tile of W (features x k), B = the input rows (k x
-// tokens), v_mfma_f32_32x32x16_bf16, fp32 accumulation. A workgroup of four
-// waves handles FT features of a group of blocks of 128 tokens: the FT x K weight
-// tile sits in LDS (padded rows) for all of them, and each wave streams the
-// K-slices of its own 32 tokens of a block straight from global memory (16
-// contiguous bytes per lane per step). The accumulator lane layout gives each
-// lane one token and runs of four consecutive features, stored as 8-byte bf16
-// writes.
-//
-// Grid. A 1-D grid in which the workgroups of one token group (all its feature
-// tiles) get the same blockIdx.x % 8, i.e. the same XCD (workgroups are dealt
-// round-robin to the 8 XCDs), and neighbouring ids, so the input rows that every
-// feature tile reads come from that XCD's L2 after the first read instead of
-// from HBM once per feature tile.
+// Two kernels, both with A = rows of W (features x k) and B = the input rows (k x
+// tokens), fp32 accumulation: the streaming one keeps all weights in registers
+// (K = 192, the shapes whose weight matrix fits), the tiled one takes any shape.
 #include "attn_common.h"
 
 namespace hla {
 namespace {
-
-constexpr int kWaves = 4;
-constexpr int kTokens = 32 * kWaves;
-constexpr int kXcds = 8;
 
 struct ProjArgs {
   const __bf16 *in;   // x [T, K] (QKV) or o [B, heads, N, d] (out)
@@ -38,213 +23,7 @@ struct ProjArgs {
   const __bf16 *w;    // [F, K]
   __bf16 *out0, *out1, *out2;  // q, k, v (QKV) or y (out, out0 only)
   int32_t T, N, K, F, heads, d, C;
-  int32_t n_ftiles, group, n_groups;  // feature tiles; token blocks per group; groups
 };
-
-// MODE 0: QKV (head split on output). MODE 1: out projection (head merge on input).
-template <int FB, int MODE>
-__global__ void __launch_bounds__(64 * kWaves) proj_kernel(ProjArgs p) {
-  constexpr int FT = 32 * FB;
-  extern __shared__ __attribute__((aligned(16))) __bf16 wl[];
-  const int WS = p.K + 8;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
-  // (token group, feature tile) of this workgroup: id L = 8 s + x goes to XCD x;
-  // its s-th slot there is feature tile s % n_ftiles of token group
-  // (s / n_ftiles) * 8 + x. The grid covers a multiple of 8 token groups, the
-  // surplus ones return here.
-  const int xcd = blockIdx.x % kXcds, s = blockIdx.x / kXcds;
-  const int group = (s / p.n_ftiles) * kXcds + xcd;
-  if (group >= p.n_groups) return;
-  const int fbase = (s % p.n_ftiles) * FT;
-
-  // weight tile -> LDS
-  const int cpr = p.K / 8;
-  for (int i = tid; i < FT * cpr; i += 64 * kWaves) {
-    const int r = i / cpr, c = i - r * cpr;
-    *reinterpret_cast<uint4 *>(wl + r * WS + c * 8) =
-        *reinterpret_cast<const uint4 *>(p.w + (int64_t)(fbase + r) * p.K + c * 8);
-  }
-  __syncthreads();
-
-  for (int blk = group * p.group; blk < group * p.group + p.group; ++blk) {
-  const int t = blk * kTokens + wave * 32 + col;
-  if (blk * kTokens >= p.T) break;
-  const bool valid = t < p.T;
-  const int tt = valid ? t : 0;
-  const int b = tt / p.N, n = tt - b * p.N;
-
-  f32x16 acc[FB];
-#pragma unroll
-  for (int f = 0; f < FB; ++f) acc[f] = f32x16{};
-
-  for (int k0 = 0; k0 < p.K; k0 += 64) {
-    bf16x8 xin[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int k = k0 + 16 * c + 8 * half;
-      const __bf16 *src;
-      if (MODE == 0) {
-        src = p.in + (p.order ? (int64_t)b * p.N + p.order[n] : (int64_t)tt) * p.K + k;
-      } else {
-        const int h = k / p.d, e = k - h * p.d;
-        src = p.in + ((int64_t)(b * p.heads + h) * p.N + n) * p.d + e;
-      }
-      xin[c] = *reinterpret_cast<const bf16x8 *>(src);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-#pragma unroll
-      for (int f = 0; f < FB; ++f) {
-        const bf16x8 wop =
-            *reinterpret_cast<const bf16x8 *>(wl + (f * 32 + col) * WS + k0 + 16 * c + 8 * half);
-        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wop, xin[c], acc[f], 0, 0, 0);
-      }
-    }
-  }
-
-  if (!valid) continue;
-#pragma unroll
-  for (int f = 0; f < FB; ++f) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int feat = fbase + f * 32 + 8 * g + 4 * half;
-      bf16x4 o4;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) o4[j] = (__bf16)acc[f][4 * g + j];
-      __bf16 *dst;
-      if (MODE == 0) {
-        const int which = feat / p.C, r = feat - which * p.C;
-        const int h = r / p.d, e = r - h * p.d;
-        __bf16 *base = which == 0 ? p.out0 : (which == 1 ? p.out1 : p.out2);
-        dst = base + ((int64_t)(b * p.heads + h) * p.N + n) * p.d + e;
-      } else {
-        dst = p.out0 + (p.order ? (int64_t)b * p.N + p.order[n] : (int64_t)tt) * p.F + feat;
-      }
-      *reinterpret_cast<bf16x4 *>(dst) = o4;
-    }
-  }
-  }
-}
-
-// Rows-resident variant (K = 16 KC <= 192): one workgroup per block of 128
-// tokens holds its rows' K-slices in registers (read from HBM once) and walks
-// every feature tile, each tile's weights copied from L2 into one of two LDS
-// buffers with the 16-byte LDS DMA while the previous tile is multiplied. Per
-// tile j: issue tile j + 1's copies, then the stores of tile j - 1 (kept in
-// registers as bf16), then the products, then a wait that leaves exactly those
-// stores in flight (the vmcnt counter is in order, so the older copies must have
-// landed) and a barrier (every wave is done with tile j's buffer). Stores never
-// hold up a wait. A lane past the last token computes and stores row T - 1 again
-// (the same bytes to the same place), so every wave issues the same number of
-// stores per tile.
-template <int KC, int FB, int MODE>
-__global__ void __launch_bounds__(64 * kWaves, 2) proj_rows_kernel(ProjArgs p) {
-  constexpr int K = 16 * KC;
-  constexpr int FT = 32 * FB;
-  constexpr int WS = K + 8;                              // padded LDS row, elements
-  constexpr int TILE_BUF = (FT * WS * 2 + 1023) / 1024 * 1024;
-  constexpr int NCOPY = TILE_BUF / 1024;                 // 1 KiB copies per tile
-  __shared__ __attribute__((aligned(16))) char wl[2 * TILE_BUF];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
-
-  // Copy instruction i of a tile fills LDS bytes [1024 i, 1024 i + 1024) of its
-  // buffer, lane l the 16 bytes at o = 1024 i + 16 l: row o / (2 WS), element
-  // (o % (2 WS)) / 2. Row padding and the slots past the last row copy a chunk
-  // of the weights that nothing reads.
-  auto issue_w = [&](int j, int buf) {
-    const int fbase = j * FT;
-    for (int i = wave; i < NCOPY; i += kWaves) {
-      const int o = 1024 * i + 16 * lane;
-      int r = o / (2 * WS), e = (o - r * 2 * WS) / 2;
-      if (r >= FT) r = FT - 1;
-      if (e >= K) e = 0;
-      lds_dma16(p.w + (int64_t)(fbase + r) * K + e, lds_addr(wl + buf * TILE_BUF + 1024 * i));
-    }
-  };
-
-  const int t = blockIdx.x * kTokens + wave * 32 + col;
-  const int tt = t < p.T ? t : p.T - 1;
-  const int b = tt / p.N, n = tt - b * p.N;
-  const int ntiles = p.F / FT;
-  constexpr int NST = 4 * FB;   // stores per lane and tile (8 bytes each)
-  // Output projection: this token's output row, loaded once, before the loop (a
-  // load of the order entry beside the stores made the compiler wait for every
-  // copy in flight on each tile).
-  int64_t yrow = (int64_t)tt;
-  if (MODE == 1 && p.order) yrow = (int64_t)b * p.N + p.order[n];
-
-  // The stores of tile j from its bf16 results (4 consecutive features each).
-  // QKV: a 32-feature block lies in one head of one of q, k, v (d % 32 == 0), so
-  // its base is wave-uniform and each lane adds a 32-bit element offset (the
-  // launcher checks that the outputs fit). Stores then share one uniform base
-  // instead of a 64-bit address per store.
-  auto store_tile = [&](int j, const bf16x4 (&o)[NST]) {
-#pragma unroll
-    for (int f = 0; f < FB; ++f) {
-      if (MODE == 0) {
-        const int f0 = j * FT + f * 32;
-        const int which = f0 / p.C, r0 = f0 - which * p.C;
-        const int h = r0 / p.d, e0 = r0 - h * p.d;
-        __bf16 *base = which == 0 ? p.out0 : (which == 1 ? p.out1 : p.out2);
-        const uint32_t row = (uint32_t)((b * p.heads + h) * p.N + n) * (uint32_t)p.d + (uint32_t)e0;
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<bf16x4 *>(base + (row + 8 * g + 4 * half)) = o[4 * f + g];
-      } else {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int feat = j * FT + f * 32 + 8 * g + 4 * half;
-          *reinterpret_cast<bf16x4 *>(p.out0 + yrow * p.F + feat) = o[4 * f + g];
-        }
-      }
-    }
-  };
-
-  issue_w(0, 0);
-  bf16x8 xin[KC];
-#pragma unroll
-  for (int c = 0; c < KC; ++c) {
-    const int k = 16 * c + 8 * half;
-    const __bf16 *src;
-    if (MODE == 0) {
-      src = p.in + (p.order ? (int64_t)b * p.N + p.order[n] : (int64_t)tt) * K + k;
-    } else {
-      const int h = k / p.d, e = k - h * p.d;
-      src = p.in + ((int64_t)(b * p.heads + h) * p.N + n) * p.d + e;
-    }
-    xin[c] = *reinterpret_cast<const bf16x8 *>(src);
-  }
-  wait_vmem_all();
-  wait_then_barrier<0>();
-
-  bf16x4 pend[NST];
-  for (int j = 0; j < ntiles; ++j) {
-    if (j + 1 < ntiles) issue_w(j + 1, (j + 1) & 1);
-    if (j > 0) store_tile(j - 1, pend);
-    const __bf16 *wt = reinterpret_cast<const __bf16 *>(wl + (j & 1) * TILE_BUF);
-    f32x16 acc[FB];
-#pragma unroll
-    for (int f = 0; f < FB; ++f) acc[f] = f32x16{};
-#pragma unroll
-    for (int c = 0; c < KC; ++c)
-#pragma unroll
-      for (int f = 0; f < FB; ++f) {
-        const bf16x8 wop = *reinterpret_cast<const bf16x8 *>(wt + (f * 32 + col) * WS + 16 * c + 8 * half);
-        acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wop, xin[c], acc[f], 0, 0, 0);
-      }
-#pragma unroll
-    for (int f = 0; f < FB; ++f)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pend[4 * f + g][q] = (__bf16)acc[f][4 * g + q];
-    if (j > 0) wait_then_barrier<NST>();
-    else wait_then_barrier<0>();
-  }
-  store_tile(ntiles - 1, pend);
-}
 
 // ---------------------------------------------------------------------------
 // Streaming kernel (weights in registers). For the layer's shapes (K = 192,
@@ -511,69 +290,224 @@ hipError_t launch_stream_any(const ProjArgs &p, hipStream_t s) {
   return p.order ? launch_stream<64, MODE, true>(p, s) : launch_stream<64, MODE, false>(p, s);
 }
 
-template <int KC, int MODE>
-hipError_t launch_rows(const ProjArgs &p, hipStream_t s) {
-  const uint32_t gx = (uint32_t)((p.T + kTokens - 1) / kTokens);
-  hipLaunchKernelGGL((proj_rows_kernel<KC, 3, MODE>), dim3(gx), dim3(64 * kWaves), 0, s, p);
+// ---------------------------------------------------------------------------
+// Tiled kernel: every other shape. y = x W^T as a matrix product of token tiles
+// (64 MT tokens) and feature tiles (64 NF features) by four waves, two by two, each
+// with MT x NF accumulators of 32 x 32 (v_mfma_f32_32x32x16_bf16, A = W rows, B = x
+// rows). What bounds it: the matrix cores and LDS together - a wave reads MT + NF
+// operands from LDS per MT * NF products, so a 64 x 96 wave tile (MT = 2, NF = 3)
+// keeps the LDS at 5/6 of its rate when the matrix cores are full, while one
+// operand read per product (a wave with one token block) fills it.
+//  - x and W come in 32 contraction steps at a time, 64-byte rows, by the 16-byte
+//    LDS DMA into a ring of three stages, two ahead (60 KiB at 128 x 192, two
+//    workgroups per CU; 48 KiB at 128 x 128, three: one's first copies and stores
+//    pass under the others' products). A fourth stage was 0-4% slower. Chunks are
+//    XOR-swizzled by row / 2, which puts the eight rows of an operand read on
+//    distinct banks.
+//  - the results are staged through LDS (the ring, once it is drained) as
+//    [token][feature] rows and leave with non-temporal 16-byte stores.
+//  - the grid gives each XCD a contiguous range of token tiles with all their
+//    feature tiles, feature tile fastest: x and W are read from HBM once and come
+//    from that XCD's L2 after that.
+constexpr int kTileWaves = 4;
+constexpr int kTileRing = 3;
+constexpr int kTileK = 32;   // contraction elements per stage
+
+struct TileArgs {
+  const __bf16 *in;
+  const int32_t *order;
+  const __bf16 *w;
+  __bf16 *out0, *out1, *out2;
+  int32_t T, N, K, F, heads, lgd, n_ftiles;
+  FastDiv ndiv;   // division by N
+  FastDiv fdiv_;  // division by n_ftiles
+};
+
+template <int MT, int NF, int MODE>
+__global__ void __launch_bounds__(64 * kTileWaves, 2) proj_tile_kernel(TileArgs p) {
+  constexpr int NW = kTileWaves, R = kTileRing;
+  constexpr int TM = 64 * MT, TF = 64 * NF;        // tokens, features of the tile
+  constexpr int ROWB = kTileK * 2;                 // bytes of a staged row
+  constexpr int XB = TM * ROWB, STAGE = XB + TF * ROWB;
+  constexpr int CX = TM * 4 / (64 * NW), CW = TF * 4 / (64 * NW);  // copies per thread
+  constexpr int LPT = CX + CW;
+  constexpr int FP = TF + 8;                       // output row pitch, elements
+  static_assert(TM * FP * 2 <= R * STAGE, "the output tile must fit the ring");
+  static_assert(LPT * (R - 2) < 64, "vmcnt range");
+  __shared__ __attribute__((aligned(16))) char lds[R * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int col = lane & 31, half = lane >> 5;
+  const int wt = wave & 1, wf = wave >> 1;         // this wave's token and feature half
+  const int logical = xcd_remap(blockIdx.x, gridDim.x);
+  const int tt = (int)fdiv((uint32_t)logical, p.fdiv_);
+  const int t0 = tt * TM, f0 = (logical - tt * p.n_ftiles) * TF;
+
+  // Source of this thread's copies at contraction step 0: slot q = (j NW + wave) 64
+  // + lane of a tile is row q / 4, chunk (q % 4) ^ (row / 2 % 4). Rows past the last
+  // token read row T - 1 and are not stored.
+  const __bf16 *xs[CX], *ws[CW];
+#pragma unroll
+  for (int j = 0; j < CX; ++j) {
+    const int q = (j * NW + wave) * 64 + lane, r = q >> 2, c = (q & 3) ^ ((r >> 1) & 3);
+    const int t = min(t0 + r, p.T - 1);
+    const int b = (int)fdiv((uint32_t)t, p.ndiv), n = t - b * p.N;
+    if (MODE == 0) xs[j] = p.in + ((int64_t)b * p.N + (p.order ? p.order[n] : n)) * p.K + 8 * c;
+    else xs[j] = p.in + (((int64_t)b * p.heads * p.N + n) << p.lgd) + 8 * c;
+  }
+#pragma unroll
+  for (int j = 0; j < CW; ++j) {
+    const int q = (j * NW + wave) * 64 + lane, r = q >> 2, c = (q & 3) ^ ((r >> 1) & 3);
+    ws[j] = p.w + (int64_t)(f0 + r) * p.K + 8 * c;
+  }
+  const int nk = p.K / kTileK;
+  auto issue = [&](int i) {
+    char *base = lds + (i % R) * STAGE;
+    const int k0 = i * kTileK;
+    // the input's step: k0 itself, or (heads merged on the fly) head k0 / d
+    const int64_t off = MODE == 0 ? (int64_t)k0
+                                  : ((int64_t)(k0 >> p.lgd) * p.N << p.lgd) + (k0 & ((1 << p.lgd) - 1));
+#pragma unroll
+    for (int j = 0; j < CX; ++j) lds_dma16(xs[j] + off, lds_addr(base + (j * NW + wave) * 1024));
+#pragma unroll
+    for (int j = 0; j < CW; ++j) lds_dma16(ws[j] + k0, lds_addr(base + XB + (j * NW + wave) * 1024));
+  };
+
+  // Operand offsets within a stage: step s = 0, 1 of 16 elements, this lane's row
+  int xoff[2], woff[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const int sw = ((2 * s + half) ^ ((col >> 1) & 3)) * 16;
+    xoff[s] = (wt * 32 * MT + col) * ROWB + sw;
+    woff[s] = XB + (wf * 32 * NF + col) * ROWB + sw;
+  }
+
+  f32x16 acc[NF][MT];
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[f][m] = f32x16{};
+
+  wait_vmem_all();   // the order entries, before the first copy
+#pragma unroll
+  for (int i = 0; i < R - 1; ++i)
+    if (i < nk) issue(i);
+  for (int i = 0; i < nk; ++i) {
+    // stage i has landed in every wave, and every wave is done with stage i - 1
+    wait_tiles_then_barrier<LPT, R - 2>(min(R - 2, nk - 1 - i));
+    if (i + R - 1 < nk) issue(i + R - 1);
+    const char *base = lds + (i % R) * STAGE;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      bf16x8 x[MT], w[NF];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) x[m] = *reinterpret_cast<const bf16x8 *>(base + xoff[s] + m * 32 * ROWB);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) w[f] = *reinterpret_cast<const bf16x8 *>(base + woff[s] + f * 32 * ROWB);
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+          acc[f][m] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[f], x[m], acc[f][m], 0, 0, 0);
+    }
+  }
+
+  // Stage as [token][feature]: lane (col, half) of block (f, m) holds token
+  // 32 m + col, slots 4g .. 4g + 3 features 8g + 4 half ..
+  wait_then_barrier<0>();   // every wave is done with the ring
+  __bf16 *st = reinterpret_cast<__bf16 *>(lds);
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        bf16x4 o4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o4[e] = (__bf16)acc[f][m][4 * g + e];
+        *reinterpret_cast<bf16x4 *>(st + ((wt * MT + m) * 32 + col) * FP + (wf * NF + f) * 32 + 8 * g + 4 * half) = o4;
+      }
+  wait_then_barrier<0>();
+  // Stores, 16 bytes per lane. QKV: chunk (token, 8 features of one head), so that a
+  // wave's consecutive lanes write whole token rows of one head.
+  constexpr int CF = TF / 8;
+  constexpr int SPW = TM * CF / (64 * NW);
+  static_assert(TM * CF % (64 * NW) == 0, "stores must split evenly");
+#pragma unroll 4
+  for (int j = 0; j < SPW; ++j) {
+    const int q = (j * NW + wave) * 64 + lane;
+    int r, c;
+    if (MODE == 0) {   // (head, token, chunk in the head)
+      const int le = p.lgd - 3;
+      c = ((q >> le) / TM << le) + (q & ((1 << le) - 1));
+      r = (q >> le) % TM;
+    } else {
+      r = q / CF;
+      c = q % CF;
+    }
+    const int t = t0 + r;
+    if (t >= p.T) continue;
+    const int b = (int)fdiv((uint32_t)t, p.ndiv), n = t - b * p.N;
+    __bf16 *dst;
+    if (MODE == 0) {
+      const int feat = f0 + 8 * c;
+      const int which = (feat >= p.K) + (feat >= 2 * p.K), e = feat - which * p.K;   // C = K
+      __bf16 *base = which == 0 ? p.out0 : (which == 1 ? p.out1 : p.out2);
+      dst = base + ((((int64_t)b * p.heads + (e >> p.lgd)) * p.N + n) << p.lgd) + (e & ((1 << p.lgd) - 1));
+    } else {
+      dst = p.out0 + ((int64_t)b * p.N + (p.order ? p.order[n] : n)) * p.F + f0 + 8 * c;
+    }
+    const u32x4 v = *reinterpret_cast<const u32x4 *>(st + r * FP + 8 * c);
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+  }
+}
+
+template <int MT, int NF, int MODE>
+hipError_t launch_tile(const ProjArgs &a, hipStream_t s) {
+  TileArgs p;
+  p.in = a.in;
+  p.order = a.order;
+  p.w = a.w;
+  p.out0 = a.out0;
+  p.out1 = a.out1;
+  p.out2 = a.out2;
+  p.T = a.T;
+  p.N = a.N;
+  p.K = a.K;
+  p.F = a.F;
+  p.heads = a.heads;
+  p.lgd = a.d == 32 ? 5 : 6;
+  p.n_ftiles = a.F / (64 * NF);
+  p.ndiv = make_fastdiv((uint32_t)a.N);
+  p.fdiv_ = make_fastdiv((uint32_t)p.n_ftiles);
+  const int64_t ttiles = ((int64_t)a.T + 64 * MT - 1) / (64 * MT);
+  hipLaunchKernelGGL((proj_tile_kernel<MT, NF, MODE>), dim3((uint32_t)(ttiles * p.n_ftiles)),
+                     dim3(64 * kTileWaves), 0, s, p);
   return hipGetLastError();
 }
 
+// Tile shape: the widest feature tile that divides F, in tiles of 128 tokens;
+// 64-token tiles where those would leave CUs without work.
 template <int MODE>
-hipError_t launch_fb(ProjArgs p, hipStream_t s) {
+hipError_t launch_tile_any(const ProjArgs &p, hipStream_t s) {
+  const int cus = device_cu_count();
+  const int nf = p.F % 192 == 0 ? 3 : (p.F % 128 == 0 ? 2 : 1);
+  const bool wide = ((int64_t)p.T + 127) / 128 * (p.F / (64 * nf)) >= cus;
+  if (nf == 3) return wide ? launch_tile<2, 3, MODE>(p, s) : launch_tile<1, 3, MODE>(p, s);
+  if (nf == 2) return wide ? launch_tile<2, 2, MODE>(p, s) : launch_tile<1, 2, MODE>(p, s);
+  return wide ? launch_tile<2, 1, MODE>(p, s) : launch_tile<1, 1, MODE>(p, s);
+}
+
+template <int MODE>
+hipError_t launch_proj(ProjArgs p, hipStream_t s) {
   // streaming kernel (weights in registers) for K = 192 with F = 576 (QKV) or
-  // F = 192 (output projection), d = 32 or 64
+  // F = 192 (output projection), d = 32 or 64: 16 x 4096 tokens 22.5 against the
+  // tiled kernel's 27 us (QKV) and 10.3 against 11.2 (output); 64 x 4096 tokens 72
+  // against 130 and 35 against 56
   if (p.K == 192 && (p.d == 32 || p.d == 64) && (MODE == 0 ? p.F == 576 : p.F == 192))
     return launch_stream_any<MODE>(p, s);
-  // rows-resident kernel where it applies: 96-feature tiles, K = 64, 128 or 192,
-  // heads of a multiple of 32 channels, outputs addressable with 32-bit offsets
-  if (p.F % 96 == 0 && p.d % 32 == 0 && (int64_t)p.T * p.F < ((int64_t)1 << 31)) {
-    if (p.K == 192) return launch_rows<12, MODE>(p, s);
-    if (p.K == 128) return launch_rows<8, MODE>(p, s);
-    if (p.K == 64) return launch_rows<4, MODE>(p, s);
-  }
-  const int64_t blocks = (p.T + kTokens - 1) / kTokens;
-  // widest feature tile whose weight slice fits the 64 KiB of LDS a workgroup
-  // gets without opting in to more
-  int fb = 1;
-  for (int cand : {6, 3, 2}) {
-    if (p.F % (32 * cand) == 0 && (int64_t)32 * cand * (p.K + 8) * 2 <= 64 * 1024) {
-      fb = cand;
-      break;
-    }
-  }
-  p.n_ftiles = p.F / (32 * fb);
-  // token blocks per workgroup (sharing one weight tile): the most of 4, 2, 1
-  // that still gives three workgroups per CU
-  int cus = 0, dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-    cus = 256;
-  p.group = 1;
-  for (int g : {4, 2}) {
-    if ((blocks + g - 1) / g * p.n_ftiles >= 3 * (int64_t)cus) {
-      p.group = g;
-      break;
-    }
-  }
-  p.n_groups = (int32_t)((blocks + p.group - 1) / p.group);
-  const int64_t groups8 = (p.n_groups + kXcds - 1) / kXcds * kXcds;
-  const uint32_t gx = (uint32_t)(groups8 * p.n_ftiles);
-  const size_t lds = (size_t)32 * fb * (p.K + 8) * 2;
-  switch (fb) {
-    case 6:
-      hipLaunchKernelGGL((proj_kernel<6, MODE>), dim3(gx), dim3(64 * kWaves), lds, s, p);
-      break;
-    case 3:
-      hipLaunchKernelGGL((proj_kernel<3, MODE>), dim3(gx), dim3(64 * kWaves), lds, s, p);
-      break;
-    case 2:
-      hipLaunchKernelGGL((proj_kernel<2, MODE>), dim3(gx), dim3(64 * kWaves), lds, s, p);
-      break;
-    default:
-      hipLaunchKernelGGL((proj_kernel<1, MODE>), dim3(gx), dim3(64 * kWaves), lds, s, p);
-      break;
-  }
-  return hipGetLastError();
+  return launch_tile_any<MODE>(p, s);
 }
 
 }  // namespace
@@ -595,7 +529,7 @@ hipError_t launch_qkv_proj(const void *x, const void *w, const int32_t *order, v
   p.F = 3 * p.C;
   p.heads = (int32_t)heads;
   p.d = (int32_t)d;
-  return launch_fb<0>(p, s);
+  return launch_proj<0>(p, s);
 }
 
 hipError_t launch_out_proj(const void *o, const void *w, const int32_t *order, void *y, int64_t B,
@@ -613,7 +547,7 @@ hipError_t launch_out_proj(const void *o, const void *w, const int32_t *order, v
   p.F = (int32_t)c_out;
   p.heads = (int32_t)heads;
   p.d = (int32_t)d;
-  return launch_fb<1>(p, s);
+  return launch_proj<1>(p, s);
 }
 
 }  // namespace hla
