@@ -162,9 +162,11 @@ __device__ __forceinline__ int swz_q(int r) {
 // tile's K/V copies; each lane reads its 32 keys' ids from there and loads the
 // 32 bias values (ordinary loads: the compiler waits for them - and, the vmcnt
 // counter being in order, for the copies issued before them - before the
-// softmax, so this mode issues each tile's copies at the end of the step two
-// tiles earlier rather than at its start).
-template <int D, int NW, int MODE>
+// softmax, so a step that does so issues its copies at its end).
+//
+// DIM: the patterns the kernel is compiled for, 1 the 1-D (Hilbert) ones, 2 the
+// row-major ones.
+template <int D, int NW, int MODE, int DIM>
 // (waves per SIMD the launch bound asks for: what the registers and LDS allow -
 // the RPB mode's windows leave room for two workgroups per CU)
 __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) : (NW == 4 ? 3 : 2))
@@ -674,18 +676,21 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     wait_then_barrier<0>();
   }
 
-  // The math of one key tile staged at st (list entry it): S^T, (mask), online
-  // softmax and O^T += V^T P^T.
-  auto tile_math = [&](const char *st, int it, auto masked) {
-    // S^T for the two 32-key blocks (independent accumulators interleaved), the
-    // RPB bias and the mask: the tile's scores, this lane's 32 of them.
-    auto scores = [&](f32x16 (&s)[2]) {
-      s[0] = f32x16{};
-      s[1] = f32x16{};
+  // The math of NB 32-key blocks (from block kb0) of the key tile staged at st (list
+  // entry it): S^T, (mask), online softmax and O^T += V^T P^T.
+  auto blocks_math = [&](const char *tile, int it, int kb0, auto nblocks, auto masked) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nblocks)::value;
+    // (32 rows leave the swizzles unchanged)
+    const char *st = tile + kb0 * 32 * D * 2;
+    // S^T for the 32-key blocks (independent accumulators interleaved), the RPB
+    // bias and the mask: the blocks' scores, this lane's 16 NB of them.
+    auto scores = [&](f32x16 (&s)[NB]) {
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb) s[kb] = f32x16{};
 #pragma unroll
       for (int c = 0; c < NCH; ++c)
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
+        for (int kb = 0; kb < NB; ++kb) {
           const bf16x8 kop = *reinterpret_cast<const bf16x8 *>(st + kaddr[c] + kb * 32 * D * 2);
           s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qop[c], s[kb], 0, 0, 0);
         }
@@ -693,19 +698,19 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
       // from the tile's staged window (entry (rq - rk - dr0) * wc + (cq - ck -
       // dc0)) or, for a tile whose window did not fit, from the table.
       if constexpr (RPB) {
-        const int32_t *kid = idx_k(it);
+        const int32_t *kid = idx_k(it) + 32 * kb0;
         const int4 pw = *reinterpret_cast<const int4 *>(lds + WINP + (it & 3) * 16);
         const int32_t w_dr0 = __builtin_amdgcn_readfirstlane(pw.x);
         const int32_t w_dc0 = __builtin_amdgcn_readfirstlane(pw.y);
         const int32_t w_wc = __builtin_amdgcn_readfirstlane(pw.z);
         const int32_t w_n = __builtin_amdgcn_readfirstlane(pw.w);
-        float bias[2][16];
+        float bias[NB][16];
         if (w_n != 0) {
           const float *win = reinterpret_cast<const float *>(lds + WIN + (it & 1) * kWinCap * 4);
-          const int32_t *term = reinterpret_cast<const int32_t *>(lds + WINB + (it & 3) * BN * 4);
+          const int32_t *term = reinterpret_cast<const int32_t *>(lds + WINB + (it & 3) * BN * 4) + 32 * kb0;
           const int32_t aq = (rq - w_dr0) * w_wc + (cq - w_dc0);
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
+          for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
               const int4 *tk = reinterpret_cast<const int4 *>(term + kb * 32 + 16 * g + 8 * half);
@@ -718,7 +723,7 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
           // all 32 bias loads first, so that they are in flight together
           const int32_t Wm1 = P.W - 1;
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
+          for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
               const int4 *ids = reinterpret_cast<const int4 *>(kid + kb * 32 + 16 * g + 8 * half);
@@ -732,27 +737,28 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
             }
         }
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
           for (int v = 0; v < 16; ++v) s[kb][v] = __builtin_fmaf(s[kb][v], a.scale, bias[kb][v]);
       }
-      if constexpr (decltype(masked)::value) mask_blocks<2>(s, R, P, tile_of(it) * BN + 8 * half);
+      if constexpr (decltype(masked)::value) mask_blocks<NB, DIM>(s, R, P, tile_of(it) * BN + 32 * kb0 + 8 * half);
     };
     // Weights p = 2^(s * smul - m) in place of the scores; returns l0 plus this
-    // lane's sum of them (two running sums, one per key block, the first seeded
-    // with l0).
-    auto weights = [&](f32x16 (&s)[2], float m, float l0) {
-      float la = l0, lb = 0.f;
+    // lane's sum of them (one running sum per key block, the first seeded with
+    // l0).
+    auto weights = [&](f32x16 (&s)[NB], float m, float l0) {
+      float ls[NB];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[0][v], smul, -m));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[1][v], smul, -m));
-        la += p0;
-        lb += p1;
-        s[0][v] = p0;
-        s[1][v] = p1;
-      }
-      return la + lb;
+      for (int kb = 0; kb < NB; ++kb) ls[kb] = kb == 0 ? l0 : 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb) {
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][v], smul, -m));
+          ls[kb] += p;
+          s[kb][v] = p;
+        }
+      return NB == 2 ? ls[0] + ls[NB - 1] : ls[0];
     };
 
     // Online softmax in the log2 domain with a lazily moved reference m_run
@@ -766,7 +772,7 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     // l_run being untouched until the tile is accepted. (Straight-line code
     // rather than a retry loop: with a loop, the compiler kept O in two register
     // sets and copied it on every tile.)
-    f32x16 s[2];
+    f32x16 s[NB];
     scores(s);
     bool slow = !primed;
     float ln = 0.f;
@@ -783,15 +789,17 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     if (slow) {
       // Max path: the reference moves only when a row's tile max exceeds it by
       // more than kRescaleSlack, so the O / l rescale stays rare.
-      float mq[4];
+      float mq[2 * NB];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < 2 * NB; ++g) {
         const f32x16 &sv = s[g >> 1];
         const int o = 8 * (g & 1);
         mq[g] = fmaxf(fmaxf(fmaxf(sv[o], sv[o + 1]), fmaxf(sv[o + 2], sv[o + 3])),
                       fmaxf(fmaxf(sv[o + 4], sv[o + 5]), fmaxf(sv[o + 6], sv[o + 7])));
       }
-      const float mx = xhalf_max(fmaxf(fmaxf(mq[0], mq[1]), fmaxf(mq[2], mq[3])));
+      float mx = fmaxf(mq[0], mq[1]);
+      if constexpr (NB == 2) mx = fmaxf(mx, fmaxf(mq[2], mq[3]));
+      mx = xhalf_max(mx);
       const float mt = mx * smul;
       const bool grow = mt > m_run + kRescaleSlack;
       if (__ballot(grow)) {
@@ -814,21 +822,43 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     l_run = ln;
     // Row sums above are fp32 sums of the unrounded weights; P goes to the PV
     // product rounded to bf16.
-    bf16x8 pop[4];
+    bf16x8 pop[2 * NB];
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < 2 * NB; ++g)
 #pragma unroll
       for (int e = 0; e < 8; ++e) pop[g][e] = (__bf16)s[g >> 1][8 * (g & 1) + e];
 
-    // O^T += V^T P^T over four 16-key steps, d blocks interleaved; V^T
+    // O^T += V^T P^T over 16-key steps, d blocks interleaved; V^T
     // operands read with the transposing LDS read right before use.
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2 * NB; ++t)
 #pragma unroll
       for (int db = 0; db < NDB; ++db) {
         const bf16x8 vop = lds_read_tr16x2(st + vbase[db] + (16 * t) * D * 2, D * 2);
         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pop[t], oacc[db], 0, 0, 0);
       }
+  };
+
+  // A full tile's two blocks together. DIM 1: a partial tile's one after the other,
+  // those without an allowed key for any query of the wave left out (their weights
+  // would be exact zeros; a band or window edge leaves a wave about half of a
+  // partial tile). Both blocks together where both are needed, beside a body for
+  // one, was slower: 189 -> 194 us on the 256x256 band, 47 -> 57 us on a 144-token
+  // window at d = 32. Not in the two-wave workgroups of d = 64, whose LDS leaves
+  // too few waves to hide a single block's latencies (1-3% slower), nor with DIM 2:
+  // a partial tile of a row-major pattern mostly needs both, and looking cost up to
+  // 15%.
+  constexpr bool SPLIT = DIM == 1 && !(D == 64 && NW == 2);
+  auto tile_math = [&](const char *st, int it, auto masked) {
+    if constexpr (decltype(masked)::value && SPLIT) {
+      const int k0 = tile_of(it) * BN;
+#pragma unroll 1
+      for (int kb = 0; kb < 2; ++kb)
+        if (__ballot(region_meets(R, P, k0 + 32 * kb, 32)))
+          blocks_math(st, it, kb, std::integral_constant<int, 1>{}, masked);
+    } else {
+      blocks_math(st, it, 0, std::integral_constant<int, 2>{}, masked);
+    }
   };
 
   // One key tile: wait for its copies, refill the ring, then S^T, (mask),
@@ -852,22 +882,28 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     if constexpr (GATHER) {
       if (it + 3 < ntot) issue_idx(it + 3);
     }
-    if constexpr (!RPB) {
+    // RPB: entry it + 1's window (its indices arrived with the wait above), then
+    // the ring refill, then entry it + 3's indices (slot (it + 3) % 4 last held
+    // entry it - 1's). With DIM 1 and four waves they go out now, so that the window
+    // has this step's products to arrive in (121 -> 118.5 us on the 128x128 window;
+    // the others lost 1-3%); else, and in a step whose bias comes straight from the table, at its end, as
+    // the compiler's wait for the table's loads covers every copy in flight.
+    const bool late =
+        RPB && (!SPLIT || *reinterpret_cast<const int32_t *>(lds + WINP + (it & 3) * 16 + 12) == 0);
+    auto refill = [&] {
+      if constexpr (RPB) {
+        if (it + 1 < ntot && wave == (it + 1) % NW) issue_window(it + 1);
+      }
       if (it + 2 < ntot) issue_tile(it + 2, nstage);
-    }
+      if constexpr (RPB) {
+        if (it + 3 < ntot) issue_idx(it + 3);
+      }
+    };
+    if (!late) refill();
     const char *st = lds + stage * STAGE;
     stage = stage == 2 ? 0 : stage + 1;
-
     tile_math(st, it, masked);
-    // RPB: at the end of the step, entry it + 1's window (its indices arrived
-    // before this step's barrier), then the ring refill (stage (it + 2) % 3 held
-    // tile it - 1, which every wave finished before this step's barrier), then
-    // entry it + 3's indices (slot (it + 3) % 4 last held entry it - 1's).
-    if constexpr (RPB) {
-      if (it + 1 < ntot && wave == (it + 1) % NW) issue_window(it + 1);
-      if (it + 2 < ntot) issue_tile(it + 2, nstage);
-      if (it + 3 < ntot) issue_idx(it + 3);
-    }
+    if (late) refill();
   };
   // Epilogue: normalise and store the rows straight from the accumulators. Lane
   // (col, half) holds, per d block and 8-row group a, the four values
@@ -1045,7 +1081,7 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
     if (!per_cu) {
       int n = 0;
       per_cu = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                   &n, reinterpret_cast<const void *>(&attn_fwd_bf16<D, NW, ATTN_HILBERT>), 64 * NW, 0) ==
+                   &n, reinterpret_cast<const void *>(&attn_fwd_bf16<D, NW, ATTN_HILBERT, 1>), 64 * NW, 0) ==
                            hipSuccess && n > 0
                    ? n : 1;
     }
@@ -1055,14 +1091,22 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
     a.hgroups = a.BH;
   }
   const int64_t blocks = (int64_t)a.hgroups * a.n_qtiles;
-  if (a.mode == ATTN_GATHER)
-    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_GATHER>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
-  else if (a.mode == ATTN_HILBERT)
-    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_HILBERT>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
-  else if (a.mode == ATTN_RPB)
-    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_RPB>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
+  const dim3 grid((uint32_t)blocks), wg(64 * NW);
+  auto run = [&](auto dim) {
+    constexpr int DIM = decltype(dim)::value;
+    if (a.mode == ATTN_GATHER)
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_GATHER, DIM>), grid, wg, 0, s, a);
+    else if (a.mode == ATTN_RPB)
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_RPB, DIM>), grid, wg, 0, s, a);
+    else
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_PLAIN, DIM>), grid, wg, 0, s, a);
+  };
+  if (a.mode == ATTN_HILBERT)
+    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_HILBERT, 1>), grid, wg, 0, s, a);
+  else if (pattern_is_1d(a.pat.kind))
+    run(std::integral_constant<int, 1>{});
   else
-    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_PLAIN>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
+    run(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

@@ -112,7 +112,9 @@ __device__ __forceinline__ void write_rows(const __bf16 *Os, __bf16 *dst, int la
 //   dq^T += K^T dS^T  A = K^T (transposing LDS reads), B = dS^T (registers)
 constexpr int kStagesDq = 3;
 
-template <int D, int NW, bool GATHER>
+// DIM: the patterns the kernels are compiled for, 1 the 1-D (Hilbert) ones, 2 the
+// row-major ones.
+template <int D, int NW, bool GATHER, int DIM>
 __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) attn_bwd_dq_bf16(AttnBwdArgs a) {
   constexpr int BM = 32 * NW;
   constexpr int NT = 64 * NW;
@@ -282,6 +284,10 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) attn_bwd_dq_bf16(Att
     // registers of both at once)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+      // (on a partial tile, a block without an allowed key for any query of the
+      // wave adds exact zeros)
+      if constexpr (decltype(masked)::value && DIM == 1)
+        if (!__ballot(region_meets(R, P, kt * BN + 32 * kb, 32))) continue;
       f32x16 s[1] = {f32x16{}}, dp = f32x16{};
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
@@ -290,7 +296,7 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 3 : 2) attn_bwd_dq_bf16(Att
         const bf16x8 vop = *reinterpret_cast<const bf16x8 *>(st + TILE + raddr[kb][c]);
         dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, gop[c], dp, 0, 0, 0);
       }
-      if constexpr (decltype(masked)::value) mask_blocks<1>(s, R, P, kt * BN + 32 * kb + 8 * half);
+      if constexpr (decltype(masked)::value) mask_blocks<1, DIM>(s, R, P, kt * BN + 32 * kb + 8 * half);
       bf16x8 dsop[2];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -343,7 +349,7 @@ constexpr bool dkdv_streams() {
   return (xch > rows ? xch : rows) <= stage;
 }
 
-template <int D, int BMQ, bool GATHER>
+template <int D, int BMQ, bool GATHER, int DIM>
 __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_bf16(AttnBwdArgs a) {
   constexpr int NT = 256;
   constexpr int CPR = D / 8;
@@ -480,12 +486,13 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_bf16(AttnBwdArgs a) {
     return hh < nitems;
   };
 
-  int raddr[QB][NCH];
+  // (block qb of the wave's rows sits 32 qb rows further: the swizzle ignores row
+  // bit 5)
+  int raddr[NCH];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int r = qh * HALF + qb * 32 + row_perm(col);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) raddr[qb][c] = r * D * 2 + (((half * NCH + c) ^ swz<D>(r)) * 16);
+  for (int c = 0; c < NCH; ++c) {
+    const int r = qh * HALF + row_perm(col);
+    raddr[c] = r * D * 2 + (((half * NCH + c) ^ swz<D>(r)) * 16);
   }
   int tbase[NDB];
 #pragma unroll
@@ -533,6 +540,69 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_bf16(AttnBwdArgs a) {
   load_kv(0);
   wait_vmem_all();
 
+  // The math of NB blocks of 32 query rows, from block qb0 of this wave's half of the
+  // query tile at sequence tile qt, staged at `tile`.
+  auto blocks_math = [&](const char *tile, int qt, int qb0, auto nblocks, auto masked) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nblocks)::value;
+    const int row0 = qh * HALF + 32 * qb0, q0 = qt * BMQ + row0;
+    const char *st = tile + 32 * qb0 * D * 2;
+    // dP - delta directly: each dP accumulator starts at -delta of its rows. Slot
+    // v of block qb is row qh*HALF + 32qb + 16(v/8) + 8half + v%8 (two runs of
+    // eight rows), i.e. two 16-byte reads per run from the staged -delta.
+    f32x16 s[NB], dp[NB];
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb) {
+      s[qb] = f32x16{};
+      const float4 *nd = reinterpret_cast<const float4 *>(tile + SND + (row0 + 32 * qb + 8 * half) * 4);
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const float4 lo = nd[4 * g], hi = nd[4 * g + 1];
+        dp[qb][8 * g + 0] = lo.x; dp[qb][8 * g + 1] = lo.y; dp[qb][8 * g + 2] = lo.z; dp[qb][8 * g + 3] = lo.w;
+        dp[qb][8 * g + 4] = hi.x; dp[qb][8 * g + 5] = hi.y; dp[qb][8 * g + 6] = hi.z; dp[qb][8 * g + 7] = hi.w;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+      for (int qb = 0; qb < NB; ++qb) {
+        const bf16x8 qa = *reinterpret_cast<const bf16x8 *>(st + raddr[c] + qb * 32 * D * 2);
+        s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kop[c], s[qb], 0, 0, 0);
+        const bf16x8 ga = *reinterpret_cast<const bf16x8 *>(st + QT + raddr[c] + qb * 32 * D * 2);
+        dp[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vop[c], dp[qb], 0, 0, 0);
+      }
+    if constexpr (decltype(masked)::value) mask_blocks<NB, DIM>(s, R, P, q0 + 8 * half);
+
+    bf16x8 pop[2 * NB], dsop[2 * NB];
+#pragma unroll
+    for (int qb = 0; qb < NB; ++qb)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        // rows qh*HALF + 32qb + 16g + 8half + (0..7): two 16-byte reads of their
+        // lse log2e, every lane of a half on the same address
+        const float4 *ls = reinterpret_cast<const float4 *>(
+            tile + SOFF + (row0 + 32 * qb + 16 * g + 8 * half) * 4);
+        const float4 la = ls[0], lb = ls[1];
+        const float l2[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int v = 8 * g + e;
+          const float p = __builtin_amdgcn_exp2f(s[qb][v] * sl2 - l2[e]);
+          pop[2 * qb + g][e] = (__bf16)p;
+          dsop[2 * qb + g][e] = (__bf16)(p * dp[qb][v]);
+        }
+      }
+
+#pragma unroll
+    for (int t = 0; t < 2 * NB; ++t)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        const bf16x8 gt = lds_read_tr16x2(st + QT + tbase[db] + (16 * t) * D * 2, D * 2);
+        dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt, pop[t], dv[db], 0, 0, 0);
+        const bf16x8 qto = lds_read_tr16x2(st + tbase[db] + (16 * t) * D * 2, D * 2);
+        dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qto, dsop[t], dk[db], 0, 0, 0);
+      }
+  };
+
   // One query tile, list entry it of item h; full and partial tiles run
   // separate loop bodies (as in the dq kernel). The items' tiles are one
   // stream through the two-stage ring: each step copies the next tile (the
@@ -553,61 +623,17 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_bf16(AttnBwdArgs a) {
     const char *st = lds + stage * STAGE;
     const int qt = tile_of(it);
 
-    // dP - delta directly: each dP accumulator starts at -delta of its rows. Slot
-    // v of block qb is row qh*HALF + 32qb + 16(v/8) + 8half + v%8 (two runs of
-    // eight rows), i.e. two 16-byte reads per run from the staged -delta.
-    f32x16 s[QB], dp[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      s[qb] = f32x16{};
-      const float4 *nd = reinterpret_cast<const float4 *>(st + SND + (qh * HALF + 32 * qb + 8 * half) * 4);
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const float4 lo = nd[4 * g], hi = nd[4 * g + 1];
-        dp[qb][8 * g + 0] = lo.x; dp[qb][8 * g + 1] = lo.y; dp[qb][8 * g + 2] = lo.z; dp[qb][8 * g + 3] = lo.w;
-        dp[qb][8 * g + 4] = hi.x; dp[qb][8 * g + 5] = hi.y; dp[qb][8 * g + 6] = hi.z; dp[qb][8 * g + 7] = hi.w;
-      }
+    // A full tile's blocks together; with DIM 1 a partial tile's one after the other,
+    // those without an allowed pair for any key of the wave left out (they add
+    // zeros).
+    if constexpr (decltype(masked)::value && DIM == 1) {
+#pragma unroll 1
+      for (int qb = 0; qb < QB; ++qb)
+        if (__ballot(region_meets(R, P, qt * BMQ + qh * HALF + 32 * qb, 32)))
+          blocks_math(st, qt, qb, std::integral_constant<int, 1>{}, masked);
+    } else {
+      blocks_math(st, qt, 0, std::integral_constant<int, QB>{}, masked);
     }
-#pragma unroll
-    for (int c = 0; c < NCH; ++c)
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        const bf16x8 qa = *reinterpret_cast<const bf16x8 *>(st + raddr[qb][c]);
-        s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa, kop[c], s[qb], 0, 0, 0);
-        const bf16x8 ga = *reinterpret_cast<const bf16x8 *>(st + QT + raddr[qb][c]);
-        dp[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga, vop[c], dp[qb], 0, 0, 0);
-      }
-    if constexpr (decltype(masked)::value) mask_blocks<QB>(s, R, P, qt * BMQ + qh * HALF + 8 * half);
-
-    bf16x8 pop[2 * QB], dsop[2 * QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        // rows qh*HALF + 32qb + 16g + 8half + (0..7): two 16-byte reads of their
-        // lse log2e, every lane of a half on the same address
-        const float4 *ls = reinterpret_cast<const float4 *>(
-            st + SOFF + (qh * HALF + 32 * qb + 16 * g + 8 * half) * 4);
-        const float4 la = ls[0], lb = ls[1];
-        const float l2[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int v = 8 * g + e;
-          const float p = __builtin_amdgcn_exp2f(s[qb][v] * sl2 - l2[e]);
-          pop[2 * qb + g][e] = (__bf16)p;
-          dsop[2 * qb + g][e] = (__bf16)(p * dp[qb][v]);
-        }
-      }
-
-#pragma unroll
-    for (int t = 0; t < 2 * QB; ++t)
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const bf16x8 gt = lds_read_tr16x2(st + QT + tbase[db] + (16 * t) * D * 2, D * 2);
-        dv[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(gt, pop[t], dv[db], 0, 0, 0);
-        const bf16x8 qto = lds_read_tr16x2(st + tbase[db] + (16 * t) * D * 2, D * 2);
-        dk[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qto, dsop[t], dk[db], 0, 0, 0);
-      }
   };
   for (h = 0; h < nitems; ++h) {
     // (a wait the compiler sees, at every item: it covers the k and v rows
@@ -684,10 +710,14 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_bf16(AttnBwdArgs a) {
 template <int D, int NW>
 hipError_t launch_dq(const AttnBwdArgs &a, hipStream_t s) {
   const int64_t blocks = (int64_t)a.BH * a.n_qtiles;
-  if (a.order)
-    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, NW, true>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_bwd_dq_bf16<D, NW, false>), dim3((uint32_t)blocks), dim3(64 * NW), 0, s, a);
+  const dim3 grid((uint32_t)blocks), wg(64 * NW);
+  auto run = [&](auto dim) {
+    constexpr int DIM = decltype(dim)::value;
+    if (a.order) hipLaunchKernelGGL((attn_bwd_dq_bf16<D, NW, true, DIM>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((attn_bwd_dq_bf16<D, NW, false, DIM>), grid, wg, 0, s, a);
+  };
+  if (pattern_is_1d(a.pat.kind)) run(std::integral_constant<int, 1>{});
+  else run(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 
@@ -729,18 +759,22 @@ hipError_t launch_dkdv(const AttnBwdArgs &a_in, hipStream_t s) {
     const int g = a.order ? 1 : 0;
     if (!per_cu[g]) {
       int n = 0;
-      const void *f = a.order ? reinterpret_cast<const void *>(&attn_bwd_dkdv_bf16<D, BMQ, true>)
-                              : reinterpret_cast<const void *>(&attn_bwd_dkdv_bf16<D, BMQ, false>);
+      const void *f = a.order ? reinterpret_cast<const void *>(&attn_bwd_dkdv_bf16<D, BMQ, true, 1>)
+                              : reinterpret_cast<const void *>(&attn_bwd_dkdv_bf16<D, BMQ, false, 1>);
       per_cu[g] = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 256, 0) == hipSuccess && n > 0 ? n : 1;
     }
     const int h = dkdv_heads_per_workgroup(a, BMQ, per_cu[g]);
     a.hgroups = (a.BH + h - 1) / h;  // groups of ceil or floor of BH / hgroups heads
   }
   const int64_t blocks = (int64_t)a.hgroups * a.n_ktiles;
-  if (a.order)
-    hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D, BMQ, true>), dim3((uint32_t)blocks), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D, BMQ, false>), dim3((uint32_t)blocks), dim3(256), 0, s, a);
+  const dim3 grid((uint32_t)blocks), wg(256);
+  auto run = [&](auto dim) {
+    constexpr int DIM = decltype(dim)::value;
+    if (a.order) hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D, BMQ, true, DIM>), grid, wg, 0, s, a);
+    else hipLaunchKernelGGL((attn_bwd_dkdv_bf16<D, BMQ, false, DIM>), grid, wg, 0, s, a);
+  };
+  if (pattern_is_1d(a.pat.kind)) run(std::integral_constant<int, 1>{});
+  else run(std::integral_constant<int, 2>{});
   return hipGetLastError();
 }
 

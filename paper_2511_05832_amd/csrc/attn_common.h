@@ -100,12 +100,6 @@ __device__ __forceinline__ Region region_of(const PatternArgs &P, int x) {
   return R;
 }
 
-__device__ __forceinline__ bool region_has(const Region &R, const PatternArgs &P, int y) {
-  if (R.one_d) return y >= R.lo && y <= R.hi;
-  const int r = (int)fdiv((uint32_t)y, P.wdiv), c = y - r * P.W;
-  return r >= R.lo && r <= R.hi && c >= R.clo && c <= R.chi;
-}
-
 // Whether region R may hold any of the positions [y0, y0 + len) (y0, len
 // wave-uniform). Exact for the 1-D patterns and for runs inside one grid row; a
 // run over several rows is tested by its rows only (never false for a run that
@@ -123,8 +117,10 @@ __device__ __forceinline__ bool region_meets(const Region &R, const PatternArgs 
 // kb holds the position base + 32*kb + 16*(v/8) + v%8 (runs of eight
 // consecutive positions; base = first position of block 0 + 8 * lane half).
 // Disallowed entries become -inf. For the row-major patterns with W a multiple
-// of 8 a run never crosses a grid row, so one division per run. The pattern
-// branch is taken once for all blocks.
+// of 8 a run never crosses a grid row, so one division per run, and with W >= 8 it
+// crosses one at most, so still one (a division per entry otherwise: fwd on
+// 71 x 93, 13 x 13 neighbourhoods, d = 64: 56 -> 52 us). The pattern branch is
+// taken once for all blocks.
 //
 // 1-D patterns: the lane's allowed slots are the offsets c = position - base in
 // [R.lo - base, R.hi - base]. A partial tile at the edge of a band or a window
@@ -134,10 +130,12 @@ __device__ __forceinline__ bool region_meets(const Region &R, const PatternArgs 
 // entry), or nothing at all when no lane of the wave loses a slot. (A row with
 // an empty interval - only padded rows past the end of the sequence, whose
 // results are never stored - may keep slots; every stored row is exact.)
-template <int NB>
+// (DIM: 1 or 2 where the kernel is compiled for the 1-D or the row-major patterns
+// alone, 0 where it takes both.)
+template <int NB, int DIM = 0>
 __device__ __forceinline__ void mask_blocks(f32x16 (&s)[NB], const Region &R,
                                             const PatternArgs &P, int base) {
-  if (R.one_d) {
+  if (DIM == 1 || (DIM == 0 && R.one_d)) {
     constexpr int CMAX = 32 * (NB - 1) + 23;   // largest offset a lane holds
     const int lo = R.lo - base, hi = R.hi - base;
     const bool cut_lo = __ballot(lo > 0) != 0;
@@ -181,12 +179,32 @@ __device__ __forceinline__ void mask_blocks(f32x16 (&s)[NB], const Region &R,
           s[kb][8 * g + t] = ok ? s[kb][8 * g + t] : -__builtin_inff();
         }
       }
+  } else if (P.W >= 8) {   // a run crosses at most one end of a grid row
+    const uint32_t rspan = (uint32_t)(R.hi - R.lo), cspan = (uint32_t)(R.chi - R.clo);
+#pragma unroll
+    for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int y0 = base + 32 * kb + 16 * g;
+        const int r = (int)fdiv((uint32_t)y0, P.wdiv), c0 = y0 - r * P.W;
+        const bool row0 = (uint32_t)(r - R.lo) <= rspan, row1 = (uint32_t)(r + 1 - R.lo) <= rspan;
+        const int left = P.W - c0;   // slots before the row's end
+        const int x0 = c0 - R.clo;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const bool next = t >= left;
+          const bool ok = (next ? row1 : row0) & ((uint32_t)(x0 + t - (next ? P.W : 0)) <= cspan);
+          s[kb][8 * g + t] = ok ? s[kb][8 * g + t] : -__builtin_inff();
+        }
+      }
   } else {
 #pragma unroll
     for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const bool ok = region_has(R, P, base + 32 * kb + 16 * (v >> 3) + (v & 7));
+        const int y = base + 32 * kb + 16 * (v >> 3) + (v & 7);
+        const int r = (int)fdiv((uint32_t)y, P.wdiv), c = y - r * P.W;
+        const bool ok = r >= R.lo && r <= R.hi && c >= R.clo && c <= R.chi;
         s[kb][v] = ok ? s[kb][v] : -__builtin_inff();
       }
   }
@@ -313,9 +331,14 @@ __device__ __forceinline__ void lds_dma16(const void *src, uint32_t dst) {
 // taking two vector instructions per copy. The offset must stay below 2^31.
 __device__ __forceinline__ void lds_dma16_at(const void *base, uint32_t off, uint32_t dst) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  // (the base read back as scalars: the compiler does not always prove it uniform)
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+  const uint32_t bhi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  const uint64_t sb = (uint64_t)bhi << 32 | blo;
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
-               : "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(dst))
+               : "v"(off), "s"(sb), "s"(__builtin_amdgcn_readfirstlane(dst))
                : "memory", "m0");
 #endif
 }
