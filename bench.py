@@ -16,8 +16,9 @@ steps, and one pair around every launch of each stage, which gives each
 kernel's average duration inside the timed region. The default workload is the
 128x128-token Hilbert window attention (B=4, heads=8, d=64, window 256), the
 same batch x heads x tokens x head_dim as the paper's headline window row
-(Table 1, I=128x128, W=16x16). The same kernel is then timed on the row-major
-16x16 window mask for the empty-tile comparison, and the CPU oracle is timed
+(Table 1, I=128x128, W=16x16). The row-major 16x16 window mask is then timed on the
+same sizes for comparison (over patches of the grid, see hla_attn_fwd; FLOPs
+counted over its allowed pairs), and the CPU oracle is timed
 on a bounded sample of the same step on the host cores.
 
 The backward pass of the same attention workload is timed the same way (a
@@ -29,8 +30,7 @@ position bias (hla_attn_fwd_rpb) is timed per call on the same inputs and
 reported under "rpb"; --no-rpb skips it.
 
 Every measured configuration (the 32x32 fp32 window, the 64x64 and 256x256
-bands, the 128x128 window, the row-major twins run through the same kernel, and
-the 64x64 layer) then gets a record under "configs": its step, its attention
+bands, the 128x128 window, the row-major twins, and the 64x64 layer) then gets a record under "configs": its step, its attention
 kernel alone (back-to-back launches) with TFLOP/s, % of its dtype's peak and a
 roofline record, and, for the Hilbert ones, the gather and scatter kernels with
 GB/s and the fraction of the 8 TB/s HBM peak. The Hilbert index is timed at
@@ -118,6 +118,15 @@ def b2b_ms(call, n):
     end.record()
     torch.cuda.synchronize()
     return start.elapsed_time(end) / n
+
+
+def rowmajor_pairs(p):
+    """Query-key pairs a row-major window or slide pattern allows per (batch, head)."""
+    def axis(n, k):
+        if p.kind == W.ROWMAJOR_WINDOW:
+            return sum(min(k, n - a) ** 2 for a in range(0, n, k))
+        return sum(min(n - 1, x + k) - max(0, x - k) + 1 for x in range(n))
+    return axis(p.H, p.p0) * axis(p.W, p.p1)
 
 
 def roofline_record(kernel, ms, nbytes, flops, dtype):
@@ -266,8 +275,13 @@ class AttnPipeline:
 
     # algorithmic figures -------------------------------------------------
     def tile_flops(self):
+        """FLOPs of the non-empty tiles (two products) and the tile counts. Row-major
+        patterns: FLOPs of the allowed pairs instead - the forward walks patches of
+        the grid where they are fewer, so the listed tiles are not what it computes."""
         tf, tp = self.mask.host_totals()
         w = self.w
+        if not w.pattern.hilbert:
+            return 4.0 * w.d * rowmajor_pairs(w.pattern) * w.B * w.heads, tf, tp
         return 4.0 * w.tile_m * w.tile_n * w.d * (tf + tp) * w.B * w.heads, tf, tp
 
     def attn_bytes(self):

@@ -197,7 +197,10 @@ hla_status hla_build_path_and_mask(int32_t H, int32_t W, int32_t *order, int32_t
 /*
  * Block-sparse attention forward (Sec. 3.1; Eq. 1's per-tile work). For every
  * (b, h) and query-tile row, walks only the listed key tiles: full tiles
- * without a mask, partial tiles with the element mask of mask->pat. Computes
+ * without a mask, partial tiles with the element mask of mask->pat. (bf16 and a
+ * row-major pattern: where patches of the grid hold the allowed pairs in fewer
+ * tiles than the lists, the kernel walks those, found from mask->pat; the lists
+ * are as the builder wrote them in either case.) Computes
  *   out[b,h,i,:] = sum_j softmax_j(scale * <q_i, k_j> | allowed(i,j)) v_j
  *   lse[b,h,i]   = ln sum_{j allowed} exp(scale * <q_i, k_j>)
  * q, k, v, out: [B, heads, N, d] of dtype; lse: float32 [B, heads, N] or NULL.

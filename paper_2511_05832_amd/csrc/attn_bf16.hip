@@ -107,6 +107,10 @@ constexpr int kWinCap = 1024;
 // (later entries, in rows with longer lists, walk the curve per tile).
 constexpr int kBlkTab = 256;
 
+// PATCH: rows of a query tile, and the most key patches a query tile may touch.
+constexpr int kPatchRows = 8;
+constexpr int kPatchTab = 512;
+
 // Bounding box {r_min, r_max, c_min, c_max} of the 64 lanes' grid cells (r, c <
 // 2^15), in every lane: both coordinates' min and max at once, as packed 16-bit
 // pairs. All 64 lanes must be active.
@@ -165,7 +169,17 @@ __device__ __forceinline__ int swz_q(int r) {
 // softmax, so a step that does so issues its copies at its end).
 //
 // DIM: the patterns the kernel is compiled for, 1 the 1-D (Hilbert) ones, 2 the
-// row-major ones.
+// row-major ones over the tile lists, 3 (PATCH) the row-major ones over patches of
+// the grid: a query tile is QR x QC grid cells instead of BM consecutive ones, a key
+// tile 8 x 8 cells instead of 64 consecutive ones, and the workgroup finds the key
+// patches its queries' rectangles touch by itself. The rectangles of consecutive
+// cells of one grid row cover many rows, each cut into 64-wide tiles of which the
+// pattern allows a fraction (33 x 33 cells on 256 x 256: 96 tiles per 128 queries,
+// 16% of their pairs allowed); those of a patch overlap in both directions (30
+// tiles, 53%). The sums run over the same allowed pairs in another order.
+// Measured: 33 x 33 on 256 x 256, d = 64, 8 heads 983 -> 304 us; 16 x 16 windows on
+// 128 x 128, 32 heads 354 -> 69 us; 13 x 13 neighbourhoods on 71 x 93, 8 heads 56 ->
+// 25 us.
 template <int D, int NW, int MODE, int DIM>
 // (waves per SIMD the launch bound asks for: what the registers and LDS allow -
 // the RPB mode's windows leave room for two workgroups per CU)
@@ -177,7 +191,10 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
   constexpr bool GATHER = MODE == ATTN_GATHER;
   constexpr bool RPB = MODE == ATTN_RPB;
   constexpr bool IDX = GATHER || RPB;
+  constexpr bool PATCH = DIM == 3;
+  static_assert(!PATCH || MODE == ATTN_PLAIN || MODE == ATTN_GATHER, "patches: plain and gather only");
   constexpr int BM = 32 * NW;
+  constexpr int QR = kPatchRows, QC = BM / QR;   // PATCH: rows and columns of a query tile
   constexpr int NT = 64 * NW;
   constexpr int CPR = D / 8;                  // 16-byte chunks per K/V row
   constexpr int TILE = BN * D * 2;            // bytes of one K or V tile
@@ -210,9 +227,12 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
                        : IDX ? IDXK + 4 * BN * 4
                        : HIL ? BLKT + kBlkTab * 4 + 32
                              : kStages * STAGE;
+  // PATCH: the list of key patches (row | column, in patches, 16 bits each)
+  constexpr int PTAB = LDSB;
+  constexpr int LDSP = PTAB + (PATCH ? kPatchTab * 4 : 0);
   static_assert(!HIL || BN == 64, "a key tile must be one 8 x 8 block of the curve");
 
-  __shared__ __attribute__((aligned(16))) char lds[LDSB];
+  __shared__ __attribute__((aligned(16))) char lds[LDSP];
   const int32_t *idx_q = reinterpret_cast<const int32_t *>(lds + IDXQ);
   auto idx_k = [&](int i) { return reinterpret_cast<const int32_t *>(lds + IDXK + (i & 3) * BN * 4); };
 
@@ -239,16 +259,60 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
 
   // This lane's query. Its Q operand (d = half*D/2 + 8c + s for step c) is
   // staged through LDS below.
-  const int qpos = qt * BM + wave * 32 + col;
+  const PatternArgs &P = a.pat;
+  // PATCH: sequence position of cell i (row by row) of this workgroup's query patch,
+  // or of a key patch; a cell past the grid's edge takes the nearest one inside
+  // (its queries are not stored, its keys masked).
+  int pr0 = 0, pc0 = 0;
+  if constexpr (PATCH) {
+    pr0 = qt / a.patch_cols * QR;
+    pc0 = (qt - qt / a.patch_cols * a.patch_cols) * QC;
+  }
+  auto q_cell = [&](int i) { return min(pr0 + i / QC, P.H - 1) * P.W + min(pc0 + i % QC, P.W - 1); };
+  auto k_cell = [&](uint32_t ent, int i) {
+    return min((int)(ent >> 16) * 8 + (i >> 3), P.H - 1) * P.W + min((int)(ent & 0xffffu) * 8 + (i & 7), P.W - 1);
+  };
+  const int lq = wave * 32 + col;
+  const int qpos = PATCH ? q_cell(lq) : qt * BM + lq;
+  const bool live = PATCH ? pr0 + lq / QC < P.H && pc0 + lq % QC < P.W : qpos < a.N;
 
   // Allowed-key region of this query (used on partial tiles only).
-  const PatternArgs &P = a.pat;
-  const Region R = region_of<true>(P, qpos);
+  Region R = region_of<true>(P, qpos);
+  if constexpr (PATCH) R.chi = min(R.chi, P.W - 1);
 
   // Tile lists, read through the scalar unit: the full tiles, then the partial.
   // (HIL: set by the prologue.)
   int nf = 0, ntot = 0, t_lo = 0, f_lo = 0, f_hi = -1;
-  if constexpr (!HIL) {
+  // PATCH: the key patches that the queries' rectangles touch, those inside every
+  // query's rectangle (full) first, tabulated by the first wave. A rectangle's ends
+  // do not decrease along an axis, so the first and the last cell bound them. (The
+  // launcher checks that the list fits the table.)
+  auto patch_of = [&](int i) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane(reinterpret_cast<const int32_t *>(lds + PTAB)[i]);
+  };
+  if constexpr (PATCH) {
+    const Region A = region_of<true>(P, q_cell(0)), Z = region_of<true>(P, q_cell(BM - 1));
+    const int R0 = max(A.lo, 0) >> 3, nR = (Z.hi >> 3) - R0 + 1;
+    const int C0 = max(A.clo, 0) >> 3, nC = (min(Z.chi, P.W - 1) >> 3) - C0 + 1;
+    // patches p with 8 p >= the last query's start and 8 p + 7 <= the first's end
+    const int fr0 = (max(Z.lo, 0) + 7) >> 3, fr1 = ((A.hi + 1) >> 3) - 1;
+    const int fc0 = (max(Z.clo, 0) + 7) >> 3, fc1 = ((min(A.chi, P.W - 1) + 1) >> 3) - 1;
+    ntot = __builtin_amdgcn_readfirstlane(min(nR * nC, kPatchTab));
+    nf = __builtin_amdgcn_readfirstlane(max(fr1 - fr0 + 1, 0) * max(fc1 - fc0 + 1, 0));
+    if (wave == 0) {
+      int32_t *tab = reinterpret_cast<int32_t *>(lds + PTAB);
+      int nfull = 0, npart = nf;
+      for (int e0 = 0; e0 < ntot; e0 += 64) {
+        const int e = e0 + lane, pr = R0 + e / nC, pc = C0 + e % nC;
+        const bool in = e < ntot, full = in && pr >= fr0 && pr <= fr1 && pc >= fc0 && pc <= fc1;
+        const uint64_t bf = __ballot(full), bp = __ballot(in && !full), below = (1ull << lane) - 1;
+        if (in) tab[full ? nfull + __popcll(bf & below) : npart + __popcll(bp & below)] = pr << 16 | pc;
+        nfull += __popcll(bf);
+        npart += __popcll(bp);
+      }
+    }
+    wait_then_barrier<63>();
+  } else if constexpr (!HIL) {
     nf = sload(a.n_full + qt);
     ntot = nf + sload(a.n_part + qt);
   }
@@ -345,6 +409,14 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
         ko[j] = (transposed ? hA1[j] : hA0[j]) ^ mirror;
         vo[j] = ko[j] ^ hX[j];
       }
+    } else if constexpr (PATCH) {
+      const uint32_t ent = patch_of(i);
+#pragma unroll
+      for (int j = 0; j < CPW; ++j) {
+        const uint32_t r = (uint32_t)k_cell(ent, krow[j]) * (uint32_t)(D * 2);
+        ko[j] = r + (uint32_t)kch[j] * 2u;
+        vo[j] = r + (uint32_t)vch[j] * 2u;
+      }
     } else {
       const int k0 = tile_of(i) * BN;
       if (k0 + BN <= a.N) {
@@ -376,8 +448,12 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
   // of the sequence read entry N - 1.
   auto issue_idx = [&](int i) {
     if constexpr (GATHER) {
-      if (wave == 0)
-        lds_dma4(a.order + min(tile_of(i) * BN + lane, a.N - 1), lds_addr(lds + IDXK + (i & 3) * BN * 4));
+      if (wave == 0) {
+        int pos;
+        if constexpr (PATCH) pos = k_cell(patch_of(i), lane);
+        else pos = min(tile_of(i) * BN + lane, a.N - 1);
+        lds_dma4(a.order + pos, lds_addr(lds + IDXK + (i & 3) * BN * 4));
+      }
     } else {
       constexpr int PER = BN / NW;   // ids per wave
       if (lane < PER)
@@ -557,7 +633,8 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     if (wave == 0) {
 #pragma unroll
       for (int c = 0; c < BM / 64; ++c)
-        lds_dma4(a.order + min(qt * BM + 64 * c + lane, a.N - 1), lds_addr(lds + IDXQ + 256 * c));
+        lds_dma4(a.order + (PATCH ? q_cell(64 * c + lane) : min(qt * BM + 64 * c + lane, a.N - 1)),
+                 lds_addr(lds + IDXQ + 256 * c));
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -575,7 +652,9 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
       } else {
         const int p = (j * NW + wave) * 64 + lane;
         const int r = p / CPR, cs = p % CPR;
-        const int64_t row = GATHER ? (int64_t)idx_q[r] : (int64_t)min(qt * BM + r, a.N - 1);
+        const int64_t row = GATHER  ? (int64_t)idx_q[r]
+                            : PATCH ? (int64_t)q_cell(r)
+                                    : (int64_t)min(qt * BM + r, a.N - 1);
         lds_dma16(Qs + row * D + (cs ^ swz_q<D>(r)) * 8, lds_addr(base + (j * NW + wave) * 1024));
       }
     }
@@ -741,7 +820,23 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
 #pragma unroll
           for (int v = 0; v < 16; ++v) s[kb][v] = __builtin_fmaf(s[kb][v], a.scale, bias[kb][v]);
       }
-      if constexpr (decltype(masked)::value) mask_blocks<NB, DIM>(s, R, P, tile_of(it) * BN + 32 * kb0 + 8 * half);
+      if constexpr (decltype(masked)::value && PATCH) {
+        // slots 8 g .. 8 g + 7 of a block are one row of the patch
+        const uint32_t ent = patch_of(it);
+        const int kr = (int)(ent >> 16) * 8 + 4 * kb0 + half, kc = (int)(ent & 0xffffu) * 8;
+        const uint32_t rspan = (uint32_t)(R.hi - R.lo), cspan = (uint32_t)(R.chi - R.clo);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const bool cok = (uint32_t)(kc + t - R.clo) <= cspan;
+#pragma unroll
+          for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              const bool ok = cok & ((uint32_t)(kr + 4 * kb + 2 * g - R.lo) <= rspan);
+              s[kb][8 * g + t] = ok ? s[kb][8 * g + t] : -__builtin_inff();
+            }
+        }
+      } else if constexpr (decltype(masked)::value) mask_blocks<NB, DIM>(s, R, P, tile_of(it) * BN + 32 * kb0 + 8 * half);
     };
     // Weights p = 2^(s * smul - m) in place of the scores; returns l0 plus this
     // lane's sum of them (one running sum per key block, the first seeded with
@@ -857,6 +952,12 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
         if (__ballot(region_meets(R, P, k0 + 32 * kb, 32)))
           blocks_math(st, it, kb, std::integral_constant<int, 1>{}, masked);
     } else {
+      if constexpr (decltype(masked)::value && PATCH) {
+        // (no allowed key in the patch for any query of the wave)
+        const uint32_t ent = patch_of(it);
+        const int kr = (int)(ent >> 16) * 8, kc = (int)(ent & 0xffffu) * 8;
+        if (!__ballot(R.lo <= kr + 7 && R.hi >= kr && R.clo <= kc + 7 && R.chi >= kc)) return;
+      }
       blocks_math(st, it, 0, std::integral_constant<int, 2>{}, masked);
     }
   };
@@ -913,9 +1014,8 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
   auto store_rows = [&](int64_t sl, int bhh) {
     const float l_tot = xhalf_sum(l_run);
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    // (queries past the end of the sequence, in a ragged last query tile, take part
-    // in the exchanges but store nothing)
-    const bool live = qpos < a.N;
+    // (queries past the end of the sequence or the grid take part in the exchanges
+    // but store nothing: live)
     const int64_t out_row = GATHER ? (int64_t)idx_q[wave * 32 + col] : HIL ? (int64_t)my_row : (int64_t)qpos;
     __bf16 *orow = static_cast<__bf16 *>(a.out) + sl + out_row * D;
   #pragma unroll
@@ -1072,6 +1172,74 @@ int heads_per_workgroup(const AttnArgs &a, int BM, int per_cu) {
   return 1;
 }
 
+// Cells of an axis that cell x's rectangle covers (row-major patterns), on the host.
+struct Span {
+  int64_t lo, hi;
+};
+Span axis_span(int kind, int64_t x, int64_t p, int64_t extent) {
+  if (kind == HLA_ROWMAJOR_SLIDE) return {std::max<int64_t>(0, x - p), std::min(extent - 1, x + p)};
+  if (kind == HLA_ROWMAJOR_WINDOW) return {x / p * p, std::min(extent - 1, x / p * p + p - 1)};
+  const int64_t s = std::min(std::max<int64_t>(x - p / 2, 0), extent - p);
+  return {s, s + p - 1};
+}
+
+// Whether a row-major pattern runs over patches of the grid (DIM 3) or over the
+// tile lists (DIM 2): whichever takes fewer key tiles, both counted at a few
+// query tiles spread over the grid (below a microsecond of host time). The times follow the counts: lists / patches
+// = 2.9 tiles ran 3.2x faster by patches (33x33 on 256x256), 1.6 1.6x (7x7 on
+// 160x160), 1.0 the same (13x13 on 32x32), 0.9 and 0.8 0.9x and 0.8x (7x7 on 64x64).
+// On widths that are no multiple of 8 the lists' mask costs more (0.76 ran 1.35x
+// faster by patches, 15x15 on 29x34, and 0.46 0.93x, 21x21 on 20x20): there
+// patches may take 1.4 times the tiles.
+bool walks_patches(const AttnArgs &a, int BM) {
+  const PatternArgs &P = a.pat;
+  if (pattern_is_1d(P.kind) || (a.mode != ATTN_PLAIN && a.mode != ATTN_GATHER)) return false;
+  if (P.H > (1 << 18) || P.W > (1 << 18)) return false;   // patch numbers fit 16 bits
+  const int64_t qc = BM / kPatchRows;
+  const int64_t nr = (P.H + kPatchRows - 1) / kPatchRows, nc = (P.W + qc - 1) / qc;
+  if ((int64_t)a.BH * nr * nc > 2147483647LL) return false;
+  // Patches along an axis under a query tile of `step` cells: mean of 16 places,
+  // and a bound (n consecutive cells touch at most (n + 14) / 8 patches).
+  auto along = [&](int64_t step, int64_t n, int64_t p, int64_t extent, int64_t *most) {
+    const int64_t reach = P.kind == HLA_ROWMAJOR_SLIDE    ? 2 * p
+                          : P.kind == HLA_ROWMAJOR_WINDOW ? 2 * (p - 1)
+                                                          : p - 1;
+    *most = (std::min(extent, step + reach) + 14) / 8;
+    const int64_t k = std::min<int64_t>(n, 16);
+    int64_t sum = 0;
+    for (int64_t i = 0; i < k; ++i) {
+      const int64_t x = i * n / k * step, y = std::min(extent - 1, x + step - 1);
+      sum += axis_span(P.kind, y, p, extent).hi / 8 - axis_span(P.kind, x, p, extent).lo / 8 + 1;
+    }
+    return (double)sum / k;
+  };
+  int64_t most_r = 0, most_c = 0;
+  const double per_r = along(kPatchRows, nr, P.p0, P.H, &most_r), per_c = along(qc, nc, P.p1, P.W, &most_c);
+  if (most_r * most_c > kPatchTab) return false;
+  // Key tiles listed for a query tile: the tiles of 64 positions that the key
+  // rows' column ranges touch (all columns when the query tile ends in another
+  // grid row than it starts in).
+  const int64_t k = std::min<int64_t>(a.n_qtiles, 8);
+  double listed = 0;
+  for (int64_t i = 0; i < k; ++i) {
+    const int32_t x = (int32_t)(i * a.n_qtiles / k * BM), y = std::min(P.N - 1, x + BM - 1);
+    const int32_t rx = x / P.W, ry = y / P.W;
+    const int64_t r0 = axis_span(P.kind, rx, P.p0, P.H).lo, r1 = axis_span(P.kind, ry, P.p0, P.H).hi;
+    const int64_t c0 = rx == ry ? axis_span(P.kind, x - rx * P.W, P.p1, P.W).lo : 0;
+    const int64_t c1 = rx == ry ? axis_span(P.kind, y - ry * P.W, P.p1, P.W).hi : P.W - 1;
+    const int64_t rows = r1 - r0 + 1, seen = std::min<int64_t>(rows, 256);
+    int64_t last = -1, tiles = 0, pos = r0 * P.W;
+    for (int64_t r = 0; r < seen; ++r, pos += P.W) {
+      const int64_t t0 = (pos + c0) / BN, t1 = (pos + c1) / BN;
+      tiles += t1 - std::max(t0 - 1, last);
+      last = t1;
+    }
+    listed += (double)tiles * rows / seen;
+  }
+  const double lists = listed / k * a.n_qtiles;
+  return per_r * nr * per_c * nc < lists * (P.W % 8 ? 1.4 : 1.0);
+}
+
 template <int D, int NW>
 hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
   AttnArgs a = a_in;
@@ -1089,6 +1257,16 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
     a.hgroups = (a.BH + h - 1) / h;  // groups of ceil or floor of BH / hgroups heads
   } else {
     a.hgroups = a.BH;
+  }
+  if (walks_patches(a, 32 * NW)) {
+    a.patch_cols = (a.pat.W + 4 * NW - 1) / (4 * NW);
+    a.n_qtiles = (a.pat.H + kPatchRows - 1) / kPatchRows * a.patch_cols;
+    const dim3 pgrid((uint32_t)((int64_t)a.BH * a.n_qtiles));
+    if (a.mode == ATTN_GATHER)
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_GATHER, 3>), pgrid, dim3(64 * NW), 0, s, a);
+    else
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_PLAIN, 3>), pgrid, dim3(64 * NW), 0, s, a);
+    return hipGetLastError();
   }
   const int64_t blocks = (int64_t)a.hgroups * a.n_qtiles;
   const dim3 grid((uint32_t)blocks), wg(64 * NW);

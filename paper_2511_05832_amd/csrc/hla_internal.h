@@ -126,6 +126,7 @@ struct AttnArgs {
   float scale, scale_log2;  // scale, scale * log2(e)
   PatternArgs pat;
   int32_t lg;               // hilbert: log2 of the grid side (N = 4^lg)
+  int32_t patch_cols;       // row-major by patches: query patches per row of patches (set by the launcher)
   int32_t hgroups;          // hilbert: groups the B * heads slices are split into (else BH)
 };
 
