@@ -136,28 +136,43 @@ def lib() -> ctypes.CDLL:
         return _lib
 
 
+# The calls below are short of host work: a small attention takes the GPU under
+# 10 us, so a call's Python time is what such a program waits for. Pointers go
+# to the C entry as plain integers (the signatures convert them), the current
+# stream's handle is read without building a torch Stream (2.1 -> 0.1 us), and a
+# tensor's checks are one test of the usual case (attn_fwd 13.0 -> 8.9 us per call).
+
 def _check(status: int):
     if status != HLA_OK:
         raise HLAError(status, lib().hla_last_error().decode(errors="replace"))
 
 
-def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+def _stream(t: torch.Tensor) -> int:
+    if _raw_stream is not None:
+        return _raw_stream(t.get_device())
+    return torch.cuda.current_stream(t.device).cuda_stream
+
+
+def _ptr(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
+
+
+_DTYPE_CODES = {torch.bfloat16: HLA_BF16, torch.float32: HLA_F32}
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return HLA_BF16
-    if t.dtype == torch.float32:
-        return HLA_F32
-    raise HLAError(HLA_ERR_UNSUPPORTED, f"dtype {t.dtype} (supported: bfloat16, float32)")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise HLAError(HLA_ERR_UNSUPPORTED, f"dtype {t.dtype} (supported: bfloat16, float32)")
+    return code
 
 
 def _require(t: torch.Tensor, name: str):
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise HLAError(HLA_ERR_INVALID_ARG, f"{name} must be a tensor")
     if t.device.type != "cuda":
@@ -322,23 +337,25 @@ def build_block_mask(pattern, tile_m: int, tile_n: int, device="cuda",
 
 
 def _attn_fwd_args(q, k, v, scale, out, lse, with_lse):
-    for t, n in ((q, "q"), (k, "k"), (v, "v")):
-        _require(t, n)
-    if q.dim() != 4 or k.shape != q.shape or v.shape != q.shape:
+    _require(q, "q")
+    _require(k, "k")
+    _require(v, "v")
+    shape, dtype = q.shape, q.dtype
+    if len(shape) != 4 or k.shape != shape or v.shape != shape:
         raise HLAError(HLA_ERR_INVALID_ARG, "q, k, v must all be [B, heads, N, d] of one shape")
-    if k.dtype != q.dtype or v.dtype != q.dtype:
+    if k.dtype != dtype or v.dtype != dtype:
         raise HLAError(HLA_ERR_INVALID_ARG, "q, k, v must share a dtype")
-    B, Hh, N, d = q.shape
+    B, Hh, N, d = shape
     if scale is None:
         scale = 1.0 / float(d) ** 0.5
     if out is None:
         out = torch.empty_like(q)
     else:
         _require(out, "out")
-    if lse is None and with_lse:
-        lse = torch.empty((B, Hh, N), dtype=torch.float32, device=q.device)
-    elif lse is not None:
+    if lse is not None:
         _require(lse, "lse")
+    elif with_lse:
+        lse = q.new_empty((B, Hh, N), dtype=torch.float32)
     return B, Hh, N, d, float(scale), out, lse
 
 
@@ -410,9 +427,10 @@ def attn_fwd_rpb(q, k, v, order, rpb, mask: BlockMask, scale: Optional[float] = 
 def _attn_bwd_args(q, k, v, out, dout, lse, scale, dq, dk, dv, stats):
     for t, n in ((q, "q"), (k, "k"), (v, "v"), (out, "out"), (dout, "dout"), (lse, "lse")):
         _require(t, n)
-    if q.dim() != 4 or any(t.shape != q.shape for t in (k, v, out, dout)):
+    shape, dtype = q.shape, q.dtype
+    if len(shape) != 4 or not (k.shape == v.shape == out.shape == dout.shape == shape):
         raise HLAError(HLA_ERR_INVALID_ARG, "q, k, v, out, dout must all be [B, heads, N, d] of one shape")
-    if any(t.dtype != q.dtype for t in (k, v, out, dout)):
+    if not (k.dtype == v.dtype == out.dtype == dout.dtype == dtype):
         raise HLAError(HLA_ERR_INVALID_ARG, "q, k, v, out, dout must share a dtype")
     B, Hh, N, d = q.shape
     if lse.dtype != torch.float32 or tuple(lse.shape) != (B, Hh, N):
@@ -423,7 +441,7 @@ def _attn_bwd_args(q, k, v, out, dout, lse, scale, dq, dk, dv, stats):
     dk = torch.empty_like(q) if dk is None else dk
     dv = torch.empty_like(q) if dv is None else dv
     if stats is None:
-        stats = torch.empty((B, Hh, N, 2), dtype=torch.float32, device=q.device)
+        stats = q.new_empty((B, Hh, N, 2), dtype=torch.float32)
     for t, n in ((dq, "dq"), (dk, "dk"), (dv, "dv"), (stats, "stats")):
         _require(t, n)
     return B, Hh, N, d, float(scale), dq, dk, dv, stats
@@ -498,7 +516,7 @@ def qkv_proj(x: torch.Tensor, w_qkv: torch.Tensor, heads: int, outs=None,
     B, N, C = x.shape
     d = C // heads
     if outs is None:
-        outs = tuple(torch.empty((B, heads, N, d), dtype=x.dtype, device=x.device) for _ in range(3))
+        outs = tuple(x.new_empty((B, heads, N, d)) for _ in range(3))
     q, k, v = outs
     if order is None:
         _check(lib().hla_qkv_proj(_ptr(x), _ptr(w_qkv), _ptr(q), _ptr(k), _ptr(v), B, N, heads, d,
@@ -522,7 +540,7 @@ def out_proj(o: torch.Tensor, w_proj: torch.Tensor, out: Optional[torch.Tensor] 
     B, Hh, N, d = o.shape
     c_out = w_proj.shape[0]
     if out is None:
-        out = torch.empty((B, N, c_out), dtype=o.dtype, device=o.device)
+        out = o.new_empty((B, N, c_out))
     if order is None:
         _check(lib().hla_out_proj(_ptr(o), _ptr(w_proj), _ptr(out), B, N, Hh, d, c_out, _stream(o)))
     else:
