@@ -31,9 +31,9 @@
 // contiguous run.
 //
 // K/V staging. K and V tiles go from global memory straight into LDS with
-// global_load_lds_dwordx4 (no register round trip), into a ring of kStages
-// stages kept kStages-1 tiles ahead. The Q tile takes the same path once, into
-// the stage the third key tile fills later. The copies are issued from inline
+// global_load_lds_dwordx4 (no register round trip), into a ring of two or three
+// stages kept one less tile ahead (see stages). The Q tile takes the same path
+// once, into the last stage, before a key tile fills it. The copies are issued from inline
 // assembly: the compiler's wait insertion would otherwise treat each
 // transposing V read as possibly overlapping a copy in flight and wait for all
 // of them - including the tile prefetched two steps ahead - on every tile. Both are stored row-major, 16-byte chunks
@@ -89,12 +89,29 @@ constexpr float kRescaleSlack = 8.f;  // log2 units the softmax reference may la
 // max-free softmax step accepts against a stale reference (2^32: far from fp32
 // overflow in O and l).
 constexpr float kFastBound = 4294967296.f;
-// LDS ring depth. Three 16 KiB stages (d = 64) let three workgroups share a
-// CU's 160 KiB; with the launch bound below that is the occupancy that measured
-// fastest. Four stages at two workgroups per CU were slower, also with a
-// software-pipelined body that computes the next tile's scores on the matrix
-// cores during the current tile's softmax; so were two stages at four per CU.
+// LDS ring depth. Three stages keep one tile in flight behind the current one and
+// one being copied into; two keep the next tile only, copied during the current
+// tile's products. At d = 64 a stage is 16 KiB: three let three four-wave
+// workgroups share a CU's 160 KiB, two let four, which the plain and fused
+// kernels' registers allow since a partial tile runs one 32-key block at a time
+// (at most 128 VGPRs). Four waves per SIMD measured, against three at three
+// stages: 256x256 band 185 -> 178 us, 56x56 neighbourhoods 26.1 -> 24.0, 1024-token
+// windows on 160x160 73 -> 68; by patches (three registers spilled) 33x33 on
+// 256x256 303 -> 290; in two-wave workgroups (64-row tiles) 66 -> 60 and 103 -> 91,
+// though a launch too small for the CUs lost 3%. The row-major list kernel needs
+// 150 VGPRs, the one-launch stream copies its Q tiles through the ring and the
+// position bias needs its indices early: they keep three.
 constexpr int kStages = 3;
+template <int D, int NW, int MODE, int DIM>
+constexpr int stages() {
+  return (MODE == ATTN_PLAIN || MODE == ATTN_GATHER) && D == 64 && DIM != 2 ? 2 : kStages;
+}
+// Waves per SIMD the launch bound asks for: what the registers and LDS allow.
+template <int D, int NW, int MODE, int DIM>
+constexpr int waves_bound() {
+  if (MODE == ATTN_RPB) return NW == 4 ? 2 : 1;
+  return stages<D, NW, MODE, DIM>() == 2 ? (NW == 4 ? 4 : MODE == ATTN_PLAIN && DIM == 1 ? 3 : 2) : (NW == 4 ? 3 : 2);
+}
 
 // Combine a value of lane l with lane l ^ 32 (the other half of a query's keys).
 __device__ __forceinline__ float xhalf_max(float x) { return fmaxf(x, __shfl_xor(x, 32)); }
@@ -148,8 +165,7 @@ __device__ __forceinline__ int swz_q(int r) {
   return (r >> 1) & 3;
 }
 
-// Launch bound (second argument: minimum waves per SIMD): three waves, i.e. at
-// most 168 VGPRs per lane and three 4-wave workgroups per CU.
+// Launch bound (second argument: minimum waves per SIMD): see waves_bound.
 //
 // MODE ATTN_GATHER: the tensors are stored in grid (row-major) order and
 // sequence position i lives in row a.order[i] (the reordering fused into the
@@ -181,9 +197,7 @@ __device__ __forceinline__ int swz_q(int r) {
 // 128 x 128, 32 heads 354 -> 69 us; 13 x 13 neighbourhoods on 71 x 93, 8 heads 56 ->
 // 25 us.
 template <int D, int NW, int MODE, int DIM>
-// (waves per SIMD the launch bound asks for: what the registers and LDS allow -
-// the RPB mode's windows leave room for two workgroups per CU)
-__global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) : (NW == 4 ? 3 : 2))
+__global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
     attn_fwd_bf16(AttnArgs a) {
   constexpr bool HIL = MODE == ATTN_HILBERT;
   // one query tile for several heads per workgroup (see the end of the kernel)
@@ -206,11 +220,11 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
   constexpr int NDB = D / 32;                 // d blocks of O^T
   static_assert(BN * CPR % NT == 0 && BM * CPR % NT == 0, "copies must split evenly");
   static_assert(BM * D * 2 <= STAGE, "the Q tile must fit one stage");
-  static_assert(kStages == 3, "the loop keeps exactly one tile in flight behind the current");
+  constexpr int NS = stages<D, NW, MODE, DIM>();   // ring depth
   static_assert(LPT < 64, "too many copies in flight for vmcnt");
   // Row-index area (GATHER): the Q tile's BM indices, then four slots of BN
   // indices for key tiles (slot i % 4 holds tile list entry i).
-  constexpr int IDXQ = kStages * STAGE;
+  constexpr int IDXQ = NS * STAGE;
   constexpr int IDXK = IDXQ + BM * 4;
   // RPB: parameters {dr0, dc0, wc, n} of four tiles' bias windows, each key's
   // window term for them (four slots of BN), the waves' query boxes, and two
@@ -226,7 +240,7 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
   constexpr int LDSB = RPB   ? WIN + 2 * kWinCap * 4
                        : IDX ? IDXK + 4 * BN * 4
                        : HIL ? BLKT + kBlkTab * 4 + 32
-                             : kStages * STAGE;
+                             : NS * STAGE;
   // PATCH: the list of key patches (row | column, in patches, 16 bits each)
   constexpr int PTAB = LDSB;
   constexpr int LDSP = PTAB + (PATCH ? kPatchTab * 4 : 0);
@@ -660,13 +674,13 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     }
   };
   if constexpr (!STREAM) {
-    issue_q(Q, 2);
+    issue_q(Q, NS - 1);
     if constexpr (RPB) {
       if (ntot > 0) issue_idx(0);
       if (ntot > 1) issue_idx(1);
     }
     if (ntot > 0) issue_tile(0, 0);
-    if (ntot > 1) issue_tile(1, 1);
+    if (NS == 3 && ntot > 1) issue_tile(1, 1);
     if constexpr (RPB) {
       if (ntot > 2) issue_idx(2);
     }
@@ -698,7 +712,7 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     qc1 = __builtin_amdgcn_readfirstlane(box.w);
   } else if constexpr (!STREAM) {
     // Q and the first key tile are in; the second may still be in flight.
-    if (ntot > 1) wait_then_barrier<LPT>();
+    if (NS == 3 && ntot > 1) wait_then_barrier<LPT>();
     else wait_then_barrier<0>();
   }
   // This lane's Q operand, from the Q tile in ring stage stg.
@@ -710,7 +724,7 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
       qop[c] = *reinterpret_cast<const bf16x8 *>(lds + stg * STAGE + r * D * 2 +
                                                  (((half * NCH + c) ^ swz_q<D>(r)) * 16));
   };
-  if constexpr (!STREAM) load_q(2);
+  if constexpr (!STREAM) load_q(NS - 1);
 
   // RPB: the bias window of list entry j, issued by one wave: the table entries
   // that this workgroup's queries and entry j's keys can address - the rectangle
@@ -972,6 +986,19 @@ __global__ void __launch_bounds__(64 * NW, MODE == ATTN_RPB ? (NW == 4 ? 2 : 1) 
     // only one issued after it) may stay in flight.
     // RPB: after tile it's window come tile it + 1's copies and entry it + 2's
     // indices.
+    if constexpr (NS == 2) {
+      // Tile it (and the indices of entry it + 1, older) are in; the other stage -
+      // the Q tile's at first, tile it - 1's then - was read before the barrier.
+      wait_then_barrier<0>();
+      if constexpr (GATHER) {
+        if (it + 3 < ntot) issue_idx(it + 3);
+      }
+      if (it + 1 < ntot) issue_tile(it + 1, stage ^ 1);
+      const char *st = lds + stage * STAGE;
+      stage ^= 1;
+      tile_math(st, it, masked);
+      return;
+    }
     if (RPB && it + 2 < ntot) wait_then_barrier<LPT + 1>();
     else if (it + 1 < ntot) wait_then_barrier<LPT>();
     else wait_then_barrier<0>();
