@@ -18,6 +18,14 @@
 // of bank conflicts. On partial tiles a wave skips a 32 x 32 block that holds no
 // allowed pair.
 //
+// Rounding: S is summed in four chains of a quarter of d (as in the forward, see
+// there), dP in two at d = 64 and one at d = 32: chains of 32 elements. With one
+// chain for both, the gradients at d = 64 were up to 25% further from float64 than
+// those of the vector-FMA kernels (49-token windows: dq 4.6e-7 against 3.7e-7; now
+// about the same). Four chains for both as well spilled 50 registers in dk/dv.
+// At d = 32 a second chain of dP takes dk/dv from 153 to 204 registers, three waves
+// per SIMD to two, and one was already nearer (dq 3.5e-7 against 3.8e-7).
+//
 //   dq kernel    one workgroup per (b*h, query tile); wave w owns 32 queries and
 //                walks the row list's key tiles; it also computes the rows'
 //                statistics (lse * log2 e, -delta; delta = <dout, out>) and stores
@@ -54,9 +62,10 @@ struct Reads {
     for (int i = 0; i < 4; ++i)
       colm[i] = 8 * half * ROW + (((e >> 2) ^ (i | (half << 2))) * 16) + (e & 3) * 4;
   }
-  // acc += rows . b over the lane's half of d
+  // acc = rows . b over the lane's half of d
+  template <int CHAINS>
   __device__ __forceinline__ void rows_times(const char *blk, const f32x4 (&b)[D / 8], f32x16 &acc) const {
-    mfma_rows_f32<D / 8>(blk, row, b, acc);
+    mfma_rows_f32<D / 8, CHAINS>(blk, row, b, acc);
   }
   // acc += columns . w
   __device__ __forceinline__ void cols_times(const char *blk, const f32x16 &w, f32x16 (&acc)[NDB]) const {
@@ -173,9 +182,9 @@ __global__ void __launch_bounds__(64 * NW * KS, 2) attn_bwd_dq_f32(AttnBwdArgs a
     const int k0 = kt * BN + 32 * kb;
     if (masked && !__ballot(region_meets(R, P, k0, 32))) return;
     const char *kblk = stage + kb * 32 * D * 4;
-    f32x16 s[1] = {f32x16{}}, dp = f32x16{};
-    rd.rows_times(kblk, q, s[0]);
-    rd.rows_times(kblk + TILE, g, dp);
+    f32x16 s[1], dp;
+    rd.template rows_times<4>(kblk, q, s[0]);
+    rd.template rows_times<D / 32>(kblk + TILE, g, dp);
     if (masked) mask_blocks<1>(s, R, P, k0 + 8 * half);
 #pragma unroll
     for (int v = 0; v < 16; ++v)
@@ -304,9 +313,9 @@ __global__ void __launch_bounds__(256, 2) attn_bwd_dkdv_f32(AttnBwdArgs a) {
     if (masked && !__ballot(region_meets(R, P, q0, 32))) return;
     const char *qblk = stage + qb * 32 * D * 4;
     const float *st = reinterpret_cast<const float *>(stage + STAT) + 32 * qb + 8 * half;
-    f32x16 s[1] = {f32x16{}}, dp = f32x16{};
-    rd.rows_times(qblk, k, s[0]);
-    rd.rows_times(qblk + TILE, v, dp);
+    f32x16 s[1], dp;
+    rd.template rows_times<4>(qblk, k, s[0]);
+    rd.template rows_times<D / 32>(qblk + TILE, v, dp);
     if (masked) mask_blocks<1>(s, R, P, q0 + 8 * half);
 #pragma unroll
     for (int x = 0; x < 4; ++x) {   // slots 4x .. 4x + 3: rows 16 (x/2) + 4 (x%2) ..

@@ -237,26 +237,35 @@ __device__ __forceinline__ int row_perm(int i) {
 // band of half-width 128: 118.6 -> 110.9 us); at d = 32, with twice the waves
 // per SIMD, it is 2% slower, so there the order is left to the compiler.
 
-// acc += rows . b: A = the block's rows, this lane's row in 16-byte chunks at
-// blk + addr[c]; b the other operand's chunks. NC chunks of four contraction steps.
-template <int NC>
+// acc = rows . b: A = the block's rows, this lane's row in 16-byte chunks at
+// blk + addr[c]; b the other operand's chunks. NC chunks of four contraction steps,
+// in CHAINS (1, 2 or 4) accumulation chains of equal parts of d, each added to the
+// sum when it ends.
+template <int NC, int CHAINS>
 __device__ __forceinline__ void mfma_rows_f32(const char *blk, const int (&addr)[NC], const f32x4 (&b)[NC],
                                               f32x16 &acc) {
+  static_assert(CHAINS == 1 || CHAINS == 2 || CHAINS == 4, "equal parts of whole chunks");
+  constexpr int PER = NC / CHAINS;   // chunks per chain
   f32x4 x[2][2];
   auto load = [&](int g) {
 #pragma unroll
     for (int e = 0; e < 2; ++e) x[g & 1][e] = *reinterpret_cast<const f32x4 *>(blk + addr[2 * g + e]);
   };
+  f32x16 part;
   load(0);
 #pragma unroll
   for (int g = 0; g < NC / 2; ++g) {
     if (g + 1 < NC / 2) load(g + 1);
     if constexpr (NC == 8) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < 2; ++e) {
+      const int c = 2 * g + e;
+      if (c % PER == 0) part = f32x16{};
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g & 1][e][i], b[2 * g + e][i], acc, 0, 0, 0);
+        part = __builtin_amdgcn_mfma_f32_32x32x2f32(x[g & 1][e][i], b[c][i], part, 0, 0, 0);
+      if (c % PER == PER - 1) acc = c < PER ? part : acc + part;
+    }
   }
 }
 
