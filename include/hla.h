@@ -197,10 +197,7 @@ hla_status hla_build_path_and_mask(int32_t H, int32_t W, int32_t *order, int32_t
 /*
  * Block-sparse attention forward (Sec. 3.1; Eq. 1's per-tile work). For every
  * (b, h) and query-tile row, walks only the listed key tiles: full tiles
- * without a mask, partial tiles with the element mask of mask->pat. (bf16 and a
- * row-major pattern: where patches of the grid hold the allowed pairs in fewer
- * tiles than the lists, the kernel walks those, found from mask->pat; the lists
- * are as the builder wrote them in either case.) Computes
+ * without a mask, partial tiles with the element mask of mask->pat. Computes
  *   out[b,h,i,:] = sum_j softmax_j(scale * <q_i, k_j> | allowed(i,j)) v_j
  *   lse[b,h,i]   = ln sum_{j allowed} exp(scale * <q_i, k_j>)
  * q, k, v, out: [B, heads, N, d] of dtype; lse: float32 [B, heads, N] or NULL.
@@ -236,6 +233,29 @@ hla_status hla_attn_fwd_perm(const void *q, const void *k, const void *v,
                              void *out, float *lse, int64_t B, int64_t heads,
                              int64_t N, int64_t d, hla_dtype dtype, float scale,
                              hla_stream_t stream);
+
+/*
+ * hla_attn_fwd (order == NULL) or hla_attn_fwd_perm (order given) for a mask whose
+ * lists are as hla_build_block_mask wrote them: the allowed pairs are those of
+ * mask->pat, so a kernel may find its tiles from the pattern and leave the lists
+ * unread. A caller that edits the lists calls hla_attn_fwd or hla_attn_fwd_perm,
+ * which always walk them.
+ * walk: HLA_WALK_LISTS walks the lists. HLA_WALK_PATCHES (bf16, row-major patterns)
+ * walks 8 x 8 patches of the grid instead: a query tile is a patch of tile_m cells,
+ * its key tiles the patches that its queries' rectangles touch; UNSUPPORTED for
+ * other patterns and f32, for a query tile that may touch more than 512 patches,
+ * and for grid sides above 2^18. HLA_WALK_AUTO takes whichever has fewer tiles, and
+ * the lists while the stream is being captured (a replay then reads them as they
+ * are at that time). The walks sum the same pairs in another order.
+ * Other arguments, support and errors as hla_attn_fwd and hla_attn_fwd_perm.
+ */
+typedef enum { HLA_WALK_AUTO = 0, HLA_WALK_LISTS = 1, HLA_WALK_PATCHES = 2 } hla_walk;
+
+hla_status hla_attn_fwd_pattern(const void *q, const void *k, const void *v,
+                                const int32_t *order, const hla_block_mask *mask,
+                                void *out, float *lse, int64_t B, int64_t heads,
+                                int64_t N, int64_t d, hla_dtype dtype, float scale,
+                                hla_walk walk, hla_stream_t stream);
 
 /*
  * hla_attn_fwd_perm with the Hilbert index and the tile lists computed inside

@@ -46,12 +46,15 @@ PATTERN_IDS = {
     "hilbert_shifted_window": 6,
 }
 
+_ROWMAJOR_IDS = frozenset(i for n, i in PATTERN_IDS.items() if n.startswith("rowmajor"))
+
 HLA_OK, HLA_ERR_INVALID_ARG, HLA_ERR_UNSUPPORTED, HLA_ERR_HIP = 0, 1, 2, 3
 HLA_F32, HLA_BF16 = 0, 1
+HLA_WALK_AUTO, HLA_WALK_LISTS, HLA_WALK_PATCHES = 0, 1, 2
 
 EXPORTED = ("hla_hilbert_perm", "hla_gather", "hla_scatter", "hla_block_mask_dims",
             "hla_build_block_mask", "hla_build_path_and_mask", "hla_attn_fwd", "hla_attn_fwd_perm",
-            "hla_attn_fwd_hilbert", "hla_attn_fwd_rpb",
+            "hla_attn_fwd_pattern", "hla_attn_fwd_hilbert", "hla_attn_fwd_rpb",
             "hla_attn_bwd", "hla_attn_bwd_perm", "hla_attn_bwd_noalloc",
             "hla_qkv_proj", "hla_out_proj", "hla_qkv_proj_perm", "hla_out_proj_perm",
             "hla_last_error", "hla_version")
@@ -109,6 +112,8 @@ def lib() -> ctypes.CDLL:
                              i64, i64, i64, i64, ctypes.c_int, f32, vp],
             "hla_attn_fwd_perm": [vp, vp, vp, vp, ctypes.POINTER(BlockMaskStruct), vp, vp,
                                   i64, i64, i64, i64, ctypes.c_int, f32, vp],
+            "hla_attn_fwd_pattern": [vp, vp, vp, vp, ctypes.POINTER(BlockMaskStruct), vp, vp,
+                                     i64, i64, i64, i64, ctypes.c_int, f32, ctypes.c_int, vp],
             "hla_attn_fwd_hilbert": [vp, vp, vp, ctypes.POINTER(PatternDesc), i32, i32, vp, vp,
                                      i64, i64, i64, i64, ctypes.c_int, f32, vp],
             "hla_attn_fwd_rpb": [vp, vp, vp, vp, vp, ctypes.POINTER(BlockMaskStruct), vp, vp,
@@ -260,46 +265,77 @@ def block_mask_dims(pattern, tile_m: int, tile_n: int) -> Tuple[int, int]:
     return nq.value, nk.value
 
 
+class _RowLists:
+    """The row lists of a BlockMask and the C struct that points to them. ``own`` is
+    True while they are known to be as the builder writes them: a row-major pattern
+    whose lists and struct no caller has been given yet. Copies of a mask share it."""
+    __slots__ = ("n_full", "n_part", "full_idx", "part_idx", "struct", "own")
+
+
+def _handed_out(name):
+    def get(self):
+        self._lists.own = False
+        return getattr(self._lists, name)
+
+    def set_(self, value):
+        self._lists.own = False
+        setattr(self._lists, name, value)
+    return property(get, set_)
+
+
 class BlockMask:
     """Device tile lists of one (pattern, tile) pair; owns its buffers.
 
     ``columns=True`` also allocates and builds the per-key-tile-column lists
-    that the backward pass walks."""
+    that the backward pass walks.
+
+    Attention walks the lists, also lists that a caller has changed. While nobody has
+    taken ``n_full``, ``n_part``, ``full_idx``, ``part_idx`` or ``struct`` from the
+    mask they can only be the builder's own; the bf16 forward of a row-major pattern
+    then finds its tiles from the pattern (hla_attn_fwd_pattern), which can be faster
+    and sums the same pairs in another order."""
+
+    n_full, n_part = _handed_out("n_full"), _handed_out("n_part")
+    full_idx, part_idx = _handed_out("full_idx"), _handed_out("part_idx")
+    struct = _handed_out("struct")
 
     def __init__(self, pattern, tile_m: int, tile_n: int, device="cuda", columns: bool = False,
                  totals: bool = True):
         nq, nk = block_mask_dims(pattern, tile_m, tile_n)
         self.pattern = pattern
         self.tile_m, self.tile_n, self.n_qtiles, self.n_ktiles = tile_m, tile_n, nq, nk
-        self.n_full = torch.empty(nq, dtype=torch.int32, device=device)
-        self.n_part = torch.empty(nq, dtype=torch.int32, device=device)
-        self.full_idx = torch.empty((nq, nk), dtype=torch.int32, device=device)
-        self.part_idx = torch.empty((nq, nk), dtype=torch.int32, device=device)
+        self._lists = r = _RowLists()
+        r.n_full = torch.empty(nq, dtype=torch.int32, device=device)
+        r.n_part = torch.empty(nq, dtype=torch.int32, device=device)
+        r.full_idx = torch.empty((nq, nk), dtype=torch.int32, device=device)
+        r.part_idx = torch.empty((nq, nk), dtype=torch.int32, device=device)
         self.totals = torch.empty(2, dtype=torch.int32, device=device)
-        self.struct = BlockMaskStruct()
-        self.struct.pat = _pattern_desc(pattern)
-        self.struct.tile_m, self.struct.tile_n = int(tile_m), int(tile_n)
-        self.struct.n_full = self.n_full.data_ptr()
-        self.struct.full_idx = self.full_idx.data_ptr()
-        self.struct.n_part = self.n_part.data_ptr()
-        self.struct.part_idx = self.part_idx.data_ptr()
+        r.struct = s = BlockMaskStruct()
+        s.pat = _pattern_desc(pattern)
+        s.tile_m, s.tile_n = int(tile_m), int(tile_n)
+        s.n_full = r.n_full.data_ptr()
+        s.full_idx = r.full_idx.data_ptr()
+        s.n_part = r.n_part.data_ptr()
+        s.part_idx = r.part_idx.data_ptr()
+        r.own = s.pat.pattern in _ROWMAJOR_IDS
         # totals=False: the build writes only the lists (the attention reads nothing
         # else); host_totals() then sums the per-row counts itself
         self.with_totals = totals
-        self.struct.totals = self.totals.data_ptr() if totals else 0
+        s.totals = self.totals.data_ptr() if totals else 0
         self.columns = columns
         if columns:
             self.n_full_t = torch.empty(nk, dtype=torch.int32, device=device)
             self.n_part_t = torch.empty(nk, dtype=torch.int32, device=device)
             self.full_idx_t = torch.empty((nk, nq), dtype=torch.int32, device=device)
             self.part_idx_t = torch.empty((nk, nq), dtype=torch.int32, device=device)
-            self.struct.n_full_t = self.n_full_t.data_ptr()
-            self.struct.full_idx_t = self.full_idx_t.data_ptr()
-            self.struct.n_part_t = self.n_part_t.data_ptr()
-            self.struct.part_idx_t = self.part_idx_t.data_ptr()
+            s.n_full_t = self.n_full_t.data_ptr()
+            s.full_idx_t = self.full_idx_t.data_ptr()
+            s.n_part_t = self.n_part_t.data_ptr()
+            s.part_idx_t = self.part_idx_t.data_ptr()
 
     def build(self):
-        _check(lib().hla_build_block_mask(ctypes.byref(self.struct), _stream(self.n_full)))
+        r = self._lists
+        _check(lib().hla_build_block_mask(ctypes.byref(r.struct), _stream(r.n_full)))
         return self
 
     def build_with_path(self, order: Optional[torch.Tensor] = None,
@@ -307,24 +343,25 @@ class BlockMask:
         """Build the lists and the Hilbert index of the pattern's grid together
         (hla_build_path_and_mask: one launch on 2^k x 2^k grids). order, rank:
         int32 [H*W] outputs, either may be None."""
-        n = self.struct.pat.H * self.struct.pat.W
+        r = self._lists
+        pat = r.struct.pat
+        n = pat.H * pat.W
         for t, name in ((order, "order"), (rank, "rank")):
             if t is not None:
                 _require(t, name)
                 if t.dtype != torch.int32 or t.numel() != n:
                     raise HLAError(HLA_ERR_INVALID_ARG, f"{name} must be int32 with H*W entries")
-        _check(lib().hla_build_path_and_mask(int(self.struct.pat.H), int(self.struct.pat.W),
-                                             _ptr(order), _ptr(rank), ctypes.byref(self.struct),
-                                             _stream(self.n_full)))
+        _check(lib().hla_build_path_and_mask(int(pat.H), int(pat.W), _ptr(order), _ptr(rank),
+                                             ctypes.byref(r.struct), _stream(r.n_full)))
         return self
 
     @property
     def N(self) -> int:
-        return self.struct.N
+        return self._lists.struct.N
 
     def host_totals(self) -> Tuple[int, int]:
         if not self.with_totals:
-            return int(self.n_full.sum().item()), int(self.n_part.sum().item())
+            return int(self._lists.n_full.sum().item()), int(self._lists.n_part.sum().item())
         t = self.totals.cpu()
         return int(t[0]), int(t[1])
 
@@ -334,6 +371,12 @@ def build_block_mask(pattern, tile_m: int, tile_n: int, device="cuda",
     """Classify all tiles and build the per-row lists (hla_build_block_mask);
     ``columns=True`` adds the per-column lists for the backward pass."""
     return BlockMask(pattern, tile_m, tile_n, device, columns).build()
+
+
+def _lists_of(mask):
+    """A mask's C struct, and whether its lists are known to be the builder's own."""
+    lists = getattr(mask, "_lists", None)
+    return (mask.struct, False) if lists is None else (lists.struct, lists.own)
 
 
 def _attn_fwd_args(q, k, v, scale, out, lse, with_lse):
@@ -364,8 +407,14 @@ def attn_fwd(q, k, v, mask: BlockMask, scale: Optional[float] = None,
              with_lse: bool = True):
     """Block-sparse attention forward (hla_attn_fwd). Returns (out, lse or None)."""
     B, Hh, N, d, scale, out, lse = _attn_fwd_args(q, k, v, scale, out, lse, with_lse)
-    _check(lib().hla_attn_fwd(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(mask.struct), _ptr(out),
-                              _ptr(lse), B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
+    struct, own = _lists_of(mask)
+    if own:
+        _check(lib().hla_attn_fwd_pattern(_ptr(q), _ptr(k), _ptr(v), 0, ctypes.byref(struct),
+                                          _ptr(out), _ptr(lse), B, Hh, N, d, _dtype_code(q), scale,
+                                          HLA_WALK_AUTO, _stream(q)))
+    else:
+        _check(lib().hla_attn_fwd(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(struct), _ptr(out),
+                                  _ptr(lse), B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return out, lse
 
 
@@ -381,9 +430,15 @@ def attn_fwd_perm(q, k, v, order, mask: BlockMask, scale: Optional[float] = None
     B, Hh, N, d, scale, out, lse = _attn_fwd_args(q, k, v, scale, out, lse, with_lse)
     if order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order has {order.numel()} entries, expected N = {N}")
-    _check(lib().hla_attn_fwd_perm(_ptr(q), _ptr(k), _ptr(v), _ptr(order), ctypes.byref(mask.struct),
-                                   _ptr(out), _ptr(lse), B, Hh, N, d, _dtype_code(q), scale,
-                                   _stream(q)))
+    struct, own = _lists_of(mask)
+    if own:
+        _check(lib().hla_attn_fwd_pattern(_ptr(q), _ptr(k), _ptr(v), _ptr(order),
+                                          ctypes.byref(struct), _ptr(out), _ptr(lse), B, Hh, N,
+                                          d, _dtype_code(q), scale, HLA_WALK_AUTO, _stream(q)))
+    else:
+        _check(lib().hla_attn_fwd_perm(_ptr(q), _ptr(k), _ptr(v), _ptr(order),
+                                       ctypes.byref(struct), _ptr(out), _ptr(lse), B, Hh, N, d,
+                                       _dtype_code(q), scale, _stream(q)))
     return out, lse
 
 
@@ -415,11 +470,12 @@ def attn_fwd_rpb(q, k, v, order, rpb, mask: BlockMask, scale: Optional[float] = 
     _require(rpb, "rpb")
     if order.dtype != torch.int32 or order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order must be int32 with N = {N} entries")
-    H, W = mask.struct.pat.H, mask.struct.pat.W
+    pat = _lists_of(mask)[0].pat
+    H, W = pat.H, pat.W
     if rpb.dtype != torch.float32 or tuple(rpb.shape) != (Hh, 2 * H - 1, 2 * W - 1):
         raise HLAError(HLA_ERR_INVALID_ARG, f"rpb must be float32 [{Hh}, {2 * H - 1}, {2 * W - 1}]")
     _check(lib().hla_attn_fwd_rpb(_ptr(q), _ptr(k), _ptr(v), _ptr(order), _ptr(rpb),
-                                  ctypes.byref(mask.struct), _ptr(out), _ptr(lse), B, Hh, N, d,
+                                  ctypes.byref(_lists_of(mask)[0]), _ptr(out), _ptr(lse), B, Hh, N, d,
                                   _dtype_code(q), scale, _stream(q)))
     return out, lse
 
@@ -456,7 +512,7 @@ def attn_bwd(q, k, v, out, dout, lse, mask: BlockMask, scale: Optional[float] = 
     B, Hh, N, d, scale, dq, dk, dv, stats = _attn_bwd_args(q, k, v, out, dout, lse, scale,
                                                            dq, dk, dv, stats)
     _check(lib().hla_attn_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                              ctypes.byref(mask.struct), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(stats),
+                              ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(stats),
                               B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return dq, dk, dv
 
@@ -473,7 +529,7 @@ def attn_bwd_perm(q, k, v, out, dout, lse, order, mask: BlockMask, scale: Option
     if order.dtype != torch.int32 or order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order must be int32 with N = {N} entries")
     _check(lib().hla_attn_bwd_perm(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                                   _ptr(order), ctypes.byref(mask.struct), _ptr(dq), _ptr(dk),
+                                   _ptr(order), ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk),
                                    _ptr(dv), _ptr(stats), B, Hh, N, d, _dtype_code(q), scale,
                                    _stream(q)))
     return dq, dk, dv
@@ -498,7 +554,7 @@ def attn_bwd_noalloc(q, k, v, out, dout, lse, mask: BlockMask, scale: Optional[f
     for t, n in ((dq, "dq"), (dk, "dk"), (dv, "dv")):
         _require(t, n)
     _check(lib().hla_attn_bwd_noalloc(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                                      ctypes.byref(mask.struct), _ptr(dq), _ptr(dk), _ptr(dv),
+                                      ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk), _ptr(dv),
                                       B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return dq, dk, dv
 

@@ -1210,6 +1210,26 @@ Span axis_span(int kind, int64_t x, int64_t p, int64_t extent) {
   return {s, s + p - 1};
 }
 
+// Whether a call can walk patches of the grid (DIM 3): a row-major pattern, plain or
+// with the reordering fused in, whose query tiles touch no more key patches than the
+// table holds (n consecutive cells touch at most (n + 14) / 8 patches), patch numbers
+// of 16 bits and a grid of 31.
+bool patches_fit(const AttnArgs &a, int BM) {
+  const PatternArgs &P = a.pat;
+  if (pattern_is_1d(P.kind) || (a.mode != ATTN_PLAIN && a.mode != ATTN_GATHER)) return false;
+  if (P.H > (1 << 18) || P.W > (1 << 18)) return false;
+  const int64_t qc = BM / kPatchRows;
+  const int64_t nr = (P.H + kPatchRows - 1) / kPatchRows, nc = (P.W + qc - 1) / qc;
+  if ((int64_t)a.BH * nr * nc > 2147483647LL) return false;
+  auto most = [&](int64_t step, int64_t p, int64_t extent) {
+    const int64_t reach = P.kind == HLA_ROWMAJOR_SLIDE    ? 2 * p
+                          : P.kind == HLA_ROWMAJOR_WINDOW ? 2 * (p - 1)
+                                                          : p - 1;
+    return (std::min(extent, step + reach) + 14) / 8;
+  };
+  return most(kPatchRows, P.p0, P.H) * most(qc, P.p1, P.W) <= kPatchTab;
+}
+
 // Whether a row-major pattern runs over patches of the grid (DIM 3) or over the
 // tile lists (DIM 2): whichever takes fewer key tiles, both counted at a few
 // query tiles spread over the grid (below a microsecond of host time). The times follow the counts: lists / patches
@@ -1218,20 +1238,13 @@ Span axis_span(int kind, int64_t x, int64_t p, int64_t extent) {
 // On widths that are no multiple of 8 the lists' mask costs more (0.76 ran 1.35x
 // faster by patches, 15x15 on 29x34, and 0.46 0.93x, 21x21 on 20x20): there
 // patches may take 1.4 times the tiles.
-bool walks_patches(const AttnArgs &a, int BM) {
+bool fewer_by_patches(const AttnArgs &a, int BM) {
+  if (!patches_fit(a, BM)) return false;
   const PatternArgs &P = a.pat;
-  if (pattern_is_1d(P.kind) || (a.mode != ATTN_PLAIN && a.mode != ATTN_GATHER)) return false;
-  if (P.H > (1 << 18) || P.W > (1 << 18)) return false;   // patch numbers fit 16 bits
   const int64_t qc = BM / kPatchRows;
   const int64_t nr = (P.H + kPatchRows - 1) / kPatchRows, nc = (P.W + qc - 1) / qc;
-  if ((int64_t)a.BH * nr * nc > 2147483647LL) return false;
-  // Patches along an axis under a query tile of `step` cells: mean of 16 places,
-  // and a bound (n consecutive cells touch at most (n + 14) / 8 patches).
-  auto along = [&](int64_t step, int64_t n, int64_t p, int64_t extent, int64_t *most) {
-    const int64_t reach = P.kind == HLA_ROWMAJOR_SLIDE    ? 2 * p
-                          : P.kind == HLA_ROWMAJOR_WINDOW ? 2 * (p - 1)
-                                                          : p - 1;
-    *most = (std::min(extent, step + reach) + 14) / 8;
+  // Patches along an axis under a query tile of `step` cells: mean of 16 places.
+  auto along = [&](int64_t step, int64_t n, int64_t p, int64_t extent) {
     const int64_t k = std::min<int64_t>(n, 16);
     int64_t sum = 0;
     for (int64_t i = 0; i < k; ++i) {
@@ -1240,9 +1253,7 @@ bool walks_patches(const AttnArgs &a, int BM) {
     }
     return (double)sum / k;
   };
-  int64_t most_r = 0, most_c = 0;
-  const double per_r = along(kPatchRows, nr, P.p0, P.H, &most_r), per_c = along(qc, nc, P.p1, P.W, &most_c);
-  if (most_r * most_c > kPatchTab) return false;
+  const double per_r = along(kPatchRows, nr, P.p0, P.H), per_c = along(qc, nc, P.p1, P.W);
   // Key tiles listed for a query tile: the tiles of 64 positions that the key
   // rows' column ranges touch (all columns when the query tile ends in another
   // grid row than it starts in).
@@ -1267,6 +1278,19 @@ bool walks_patches(const AttnArgs &a, int BM) {
   return per_r * nr * per_c * nc < lists * (P.W % 8 ? 1.4 : 1.0);
 }
 
+// The walk of a call that leaves it to the library. While a stream is captured it is
+// the lists': a replay must find what the lists hold then.
+bool walks_patches(const AttnArgs &a, int BM, hipStream_t s) {
+  if (a.walk != HLA_WALK_AUTO) return a.walk == HLA_WALK_PATCHES;
+  if (!fewer_by_patches(a, BM)) return false;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st == hipStreamCaptureStatusNone;
+}
+
 template <int D, int NW>
 hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
   AttnArgs a = a_in;
@@ -1285,7 +1309,7 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
   } else {
     a.hgroups = a.BH;
   }
-  if (walks_patches(a, 32 * NW)) {
+  if (walks_patches(a, 32 * NW, s)) {
     a.patch_cols = (a.pat.W + 4 * NW - 1) / (4 * NW);
     a.n_qtiles = (a.pat.H + kPatchRows - 1) / kPatchRows * a.patch_cols;
     const dim3 pgrid((uint32_t)((int64_t)a.BH * a.n_qtiles));
@@ -1316,6 +1340,8 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
 }
 
 }  // namespace
+
+bool attn_patches_fit(const AttnArgs &a, int tile_m) { return patches_fit(a, tile_m); }
 
 hipError_t launch_attn_bf16(const AttnArgs &a, int d, int tile_m, int tile_n,
                             hipStream_t s) {

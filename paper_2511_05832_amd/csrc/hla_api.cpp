@@ -344,7 +344,8 @@ extern "C" {
 static hla_status attn_fwd(const void *q, const void *k, const void *v, const int32_t *order,
                            const float *rpb, int mode, const hla_block_mask *mask, void *out,
                            float *lse, int64_t B, int64_t heads, int64_t N, int64_t d,
-                           hla_dtype dtype, float scale, hla_stream_t stream, const char *name) {
+                           hla_dtype dtype, float scale, hla_stream_t stream, const char *name,
+                           hla_walk walk = HLA_WALK_LISTS) {
   hla_status st;
   if ((st = check_tensor_args(q, "q")) != HLA_OK) return st;
   if ((st = check_tensor_args(k, "k")) != HLA_OK) return st;
@@ -381,9 +382,12 @@ static hla_status attn_fwd(const void *q, const void *k, const void *v, const in
   a.scale_log2 = (float)((double)scale * 1.4426950408889634074);
   a.pat = hla::make_pattern_args(mask->pat);
   a.lg = 0;
+  a.walk = walk;
   a.patch_cols = 0;
   a.hgroups = (int32_t)BH;
   while ((1 << a.lg) < mask->pat.W) ++a.lg;
+  if (walk == HLA_WALK_PATCHES && (dtype != HLA_BF16 || !hla::attn_patches_fit(a, mask->tile_m)))
+    return fail(HLA_ERR_UNSUPPORTED, "this pattern, grid or dtype cannot walk patches");
   hipError_t e = dtype == HLA_BF16
                      ? hla::launch_attn_bf16(a, (int)d, mask->tile_m, mask->tile_n, (hipStream_t)stream)
                      : hla::launch_attn_f32(a, (int)d, mask->tile_m, mask->tile_n, (hipStream_t)stream);
@@ -397,17 +401,39 @@ hla_status hla_attn_fwd(const void *q, const void *k, const void *v, const hla_b
                   dtype, scale, stream, "hla_attn_fwd");
 }
 
-hla_status hla_attn_fwd_perm(const void *q, const void *k, const void *v, const int32_t *order,
-                             const hla_block_mask *mask, void *out, float *lse, int64_t B,
-                             int64_t heads, int64_t N, int64_t d, hla_dtype dtype, float scale,
-                             hla_stream_t stream) {
-  if (!order) return fail(HLA_ERR_INVALID_ARG, "order is NULL");
+// The forward with the reordering fused in.
+static hla_status attn_fwd_perm(const void *q, const void *k, const void *v, const int32_t *order,
+                                const hla_block_mask *mask, void *out, float *lse, int64_t B,
+                                int64_t heads, int64_t N, int64_t d, hla_dtype dtype, float scale,
+                                hla_stream_t stream, const char *name, hla_walk walk) {
   if (!aligned(order, 16)) return fail(HLA_ERR_INVALID_ARG, "order is not 16-byte aligned");
   for (const void *t : {q, k, v, (const void *)out})
     if (t && overlaps(order, N * 4, t, B * heads * N * d * dtype_size(dtype)))
       return fail(HLA_ERR_INVALID_ARG, "order overlaps a tensor");
   return attn_fwd(q, k, v, order, nullptr, hla::ATTN_GATHER, mask, out, lse, B, heads, N, d,
-                  dtype, scale, stream, "hla_attn_fwd_perm");
+                  dtype, scale, stream, name, walk);
+}
+
+hla_status hla_attn_fwd_perm(const void *q, const void *k, const void *v, const int32_t *order,
+                             const hla_block_mask *mask, void *out, float *lse, int64_t B,
+                             int64_t heads, int64_t N, int64_t d, hla_dtype dtype, float scale,
+                             hla_stream_t stream) {
+  if (!order) return fail(HLA_ERR_INVALID_ARG, "order is NULL");
+  return attn_fwd_perm(q, k, v, order, mask, out, lse, B, heads, N, d, dtype, scale, stream,
+                       "hla_attn_fwd_perm", HLA_WALK_LISTS);
+}
+
+hla_status hla_attn_fwd_pattern(const void *q, const void *k, const void *v, const int32_t *order,
+                                const hla_block_mask *mask, void *out, float *lse, int64_t B,
+                                int64_t heads, int64_t N, int64_t d, hla_dtype dtype, float scale,
+                                hla_walk walk, hla_stream_t stream) {
+  if (walk != HLA_WALK_AUTO && walk != HLA_WALK_LISTS && walk != HLA_WALK_PATCHES)
+    return fail(HLA_ERR_INVALID_ARG, "unknown walk %d", (int)walk);
+  if (order)
+    return attn_fwd_perm(q, k, v, order, mask, out, lse, B, heads, N, d, dtype, scale, stream,
+                         "hla_attn_fwd_pattern", walk);
+  return attn_fwd(q, k, v, nullptr, nullptr, hla::ATTN_PLAIN, mask, out, lse, B, heads, N, d,
+                  dtype, scale, stream, "hla_attn_fwd_pattern", walk);
 }
 
 hla_status hla_attn_fwd_hilbert(const void *q, const void *k, const void *v,

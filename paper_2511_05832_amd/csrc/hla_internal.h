@@ -126,10 +126,13 @@ struct AttnArgs {
   float scale, scale_log2;  // scale, scale * log2(e)
   PatternArgs pat;
   int32_t lg;               // hilbert: log2 of the grid side (N = 4^lg)
+  int32_t walk;             // HLA_WALK_*
   int32_t patch_cols;       // row-major by patches: query patches per row of patches (set by the launcher)
   int32_t hgroups;          // hilbert: groups the B * heads slices are split into (else BH)
 };
 
+// Whether a bf16 call can walk patches of the grid (HLA_WALK_PATCHES).
+bool attn_patches_fit(const AttnArgs &a, int tile_m);
 hipError_t launch_attn_bf16(const AttnArgs &a, int d, int tile_m, int tile_n,
                             hipStream_t s);
 hipError_t launch_attn_f32(const AttnArgs &a, int d, int tile_m, int tile_n,
