@@ -1232,7 +1232,8 @@ bool patches_fit(const AttnArgs &a, int BM) {
 
 // Whether a row-major pattern runs over patches of the grid (DIM 3) or over the
 // tile lists (DIM 2): whichever takes fewer key tiles, both counted at a few
-// query tiles spread over the grid (below a microsecond of host time). The times follow the counts: lists / patches
+// query tiles spread over the grid: at most 64 grid rows each, 0.2-0.9 us of host time
+// (2.8 us when every row was counted, radius 250 on 4096x64). The times follow the counts: lists / patches
 // = 2.9 tiles ran 3.2x faster by patches (33x33 on 256x256), 1.6 1.6x (7x7 on
 // 160x160), 1.0 the same (13x13 on 32x32), 0.9 and 0.8 0.9x and 0.8x (7x7 on 64x64).
 // On widths that are no multiple of 8 the lists' mask costs more (0.76 ran 1.35x
@@ -1256,7 +1257,9 @@ bool fewer_by_patches(const AttnArgs &a, int BM) {
   const double per_r = along(kPatchRows, nr, P.p0, P.H), per_c = along(qc, nc, P.p1, P.W);
   // Key tiles listed for a query tile: the tiles of 64 positions that the key
   // rows' column ranges touch (all columns when the query tile ends in another
-  // grid row than it starts in).
+  // grid row than it starts in). The rows' cuts into tiles repeat every `period` rows.
+  int64_t period = 1;
+  while ((period * P.W) % BN) period *= 2;
   const int64_t k = std::min<int64_t>(a.n_qtiles, 8);
   double listed = 0;
   for (int64_t i = 0; i < k; ++i) {
@@ -1265,14 +1268,19 @@ bool fewer_by_patches(const AttnArgs &a, int BM) {
     const int64_t r0 = axis_span(P.kind, rx, P.p0, P.H).lo, r1 = axis_span(P.kind, ry, P.p0, P.H).hi;
     const int64_t c0 = rx == ry ? axis_span(P.kind, x - rx * P.W, P.p1, P.W).lo : 0;
     const int64_t c1 = rx == ry ? axis_span(P.kind, y - ry * P.W, P.p1, P.W).hi : P.W - 1;
-    const int64_t rows = r1 - r0 + 1, seen = std::min<int64_t>(rows, 256);
-    int64_t last = -1, tiles = 0, pos = r0 * P.W;
-    for (int64_t r = 0; r < seen; ++r, pos += P.W) {
-      const int64_t t0 = (pos + c0) / BN, t1 = (pos + c1) / BN;
+    // (r: rows after the first, in whole periods and `left` more)
+    const int64_t r = r1 - r0, left = r & (period - 1);
+    uint64_t pos = (uint64_t)r0 * P.W;
+    int64_t last = (int64_t)((pos + c1) / BN), tiles = 0, tail = 0;
+    listed += last - (int64_t)((pos + c0) / BN) + 1;
+    for (int64_t e = 0; e < std::min(r, period); ++e) {
+      pos += P.W;
+      const int64_t t0 = (int64_t)((pos + c0) / BN), t1 = (int64_t)((pos + c1) / BN);
       tiles += t1 - std::max(t0 - 1, last);
       last = t1;
+      if (e + 1 == left) tail = tiles;
     }
-    listed += (double)tiles * rows / seen;
+    listed += tiles * (r / period) + tail;
   }
   const double lists = listed / k * a.n_qtiles;
   return per_r * nr * per_c * nc < lists * (P.W % 8 ? 1.4 : 1.0);
