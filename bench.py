@@ -17,7 +17,7 @@ kernel's average duration inside the timed region. The default workload is the
 128x128-token Hilbert window attention (B=4, heads=8, d=64, window 256), the
 same batch x heads x tokens x head_dim as the paper's headline window row
 (Table 1, I=128x128, W=16x16). The row-major 16x16 window mask is then timed on the
-same sizes for comparison (over patches of the grid, see hla_attn_fwd; FLOPs
+same sizes for comparison (over patches of the grid, see hla_attn_fwd_pattern; FLOPs
 counted over its allowed pairs), and the CPU oracle is timed
 on a bounded sample of the same step on the host cores.
 
@@ -121,11 +121,15 @@ def b2b_ms(call, n):
 
 
 def rowmajor_pairs(p):
-    """Query-key pairs a row-major window or slide pattern allows per (batch, head)."""
+    """Query-key pairs a row-major pattern allows per (batch, head)."""
     def axis(n, k):
         if p.kind == W.ROWMAJOR_WINDOW:
             return sum(min(k, n - a) ** 2 for a in range(0, n, k))
-        return sum(min(n - 1, x + k) - max(0, x - k) + 1 for x in range(n))
+        if p.kind == W.ROWMAJOR_SLIDE:
+            return sum(min(n - 1, x + k) - max(0, x - k) + 1 for x in range(n))
+        if p.kind == W.ROWMAJOR_NEIGHBORHOOD:
+            return n * k
+        raise ValueError(f"not a row-major pattern: {p.kind}")
     return axis(p.H, p.p0) * axis(p.W, p.p1)
 
 
@@ -275,14 +279,19 @@ class AttnPipeline:
 
     # algorithmic figures -------------------------------------------------
     def tile_flops(self):
-        """FLOPs of the non-empty tiles (two products) and the tile counts. Row-major
-        patterns: FLOPs of the allowed pairs instead - the forward walks patches of
-        the grid where they are fewer, so the listed tiles are not what it computes."""
+        """FLOPs of the listed tiles (two products) and the tile counts."""
         tf, tp = self.mask.host_totals()
         w = self.w
-        if not w.pattern.hilbert:
-            return 4.0 * w.d * rowmajor_pairs(w.pattern) * w.B * w.heads, tf, tp
         return 4.0 * w.tile_m * w.tile_n * w.d * (tf + tp) * w.B * w.heads, tf, tp
+
+    def attn_flops(self):
+        """FLOPs of the forward and what they are counted over: the listed tiles or, for
+        row-major patterns, the allowed pairs - their forward walks patches of the grid
+        where those are fewer, so the listed tiles are not what it computes."""
+        w = self.w
+        if w.pattern.hilbert:
+            return self.tile_flops()[0], "nonempty_tiles"
+        return 4.0 * w.d * rowmajor_pairs(w.pattern) * w.B * w.heads, "allowed_pairs"
 
     def attn_bytes(self):
         """q, k, v, out once each plus the fp32 log-sum-exp: 4 N d s + 4 N per (b, h)."""
@@ -451,6 +460,9 @@ class LayerPipeline:
         tf, tp = self.mask.host_totals()
         w = self.w
         return 4.0 * w.tile_m * w.tile_n * w.d * (tf + tp) * w.B * w.heads, tf, tp
+
+    def attn_flops(self):
+        return self.tile_flops()[0], "nonempty_tiles"
 
     def attn_bytes(self):
         w = self.w
@@ -693,7 +705,8 @@ def time_rpb(pipe, steps, warmup):
 def summarize(pipe, timing):
     ms_step, eager_ms, passes = timing
     T = pipe.timer
-    flops, tf, tp = pipe.tile_flops()
+    tile_flops, tf, tp = pipe.tile_flops()
+    flops, basis = pipe.attn_flops()
     w = pipe.w
     attn_ms = T.mean_ms("attn")
     attn_tflops = flops / (attn_ms * 1e-3) / 1e12
@@ -706,11 +719,12 @@ def summarize(pipe, timing):
         "ms_per_step_stream": passes["stream"],
         "step_timing": "graph" if passes["graph"] <= passes["stream"] else "stream",
         "attn_ms": attn_ms,
-        "attn_tile_tflops": attn_tflops,
+        f"attn_tflops_{basis}": attn_tflops,
         "attn_pct_peak": 100.0 * attn_tflops / peak,
         "attn_hbm_gbs": pipe.attn_bytes() / (attn_ms * 1e-3) / 1e9,
         "tiles_full": tf, "tiles_partial": tp,
-        "tile_flops": flops,
+        "tile_flops": tile_flops,
+        "attn_flops": flops, "attn_flops_of": basis,
         "stages_ms": {n: T.mean_ms(n) for n in T.pairs},
     }
     if "gather" in T.pairs:
@@ -745,10 +759,13 @@ def attn_config_record(w, hla, steps, warmup, fused_step=True):
     comp = make_pipeline(w, hla)
     rc = summarize(comp, run_timed(comp, steps, warmup))
     kms_c = comp.kernel_ms(n)
-    flops, tf, tp = comp.tile_flops()
+    tile_flops, tf, tp = comp.tile_flops()
+    flops, basis = comp.attn_flops()
     nbytes = comp.attn_bytes()
     rec["tiles"] = {"full": tf, "partial": tp}
-    rec["tile_flops"] = flops
+    rec["tile_flops"] = tile_flops
+    if basis == "allowed_pairs":
+        rec["pair_flops"] = flops
     if comp.hilbert:
         pb = comp.perm_bytes_per_tensor()
         rec["perm"] = {"gather": perm_record(comp.perm_kernel_ms(n), pb,
@@ -782,7 +799,7 @@ def attn_config_record(w, hla, steps, warmup, fused_step=True):
         "ms_per_step": res["ms_per_step"], "ms_per_step_eager": res["ms_per_step_eager"],
         "value": flops / (res["ms_per_step"] * 1e-3) / 1e12, "unit": "TFLOP/s",
         "attn_ms_per_call": kms,
-        "attn_tflops_nonempty_tiles": flops / (kms * 1e-3) / 1e12,
+        f"attn_tflops_{basis}": flops / (kms * 1e-3) / 1e12,
         "attn_pct_peak": 100.0 * flops / (kms * 1e-3) / 1e12 / peak,
         "peak_tflops": peak,
         "roofline": roofline_record(kernel, kms, nbytes, flops, w.dtype),
@@ -1086,7 +1103,7 @@ def main():
                          for sd in (128, 256, 4096)}
         print(f"[bench] hilbert index: {json.dumps(hilbert_index)}", file=sys.stderr, flush=True)
 
-    flops = res["tile_flops"]
+    flops, basis = res["attn_flops"], res["attn_flops_of"]
     # the dominant kernel's average duration: back-to-back launches between one
     # event pair where measured, else the eager pass's per-stage events
     attn_s = res.get("attn_kernel_ms", res["attn_ms"]) * 1e-3
@@ -1154,7 +1171,7 @@ def main():
                  if getattr(getattr(w, "pattern", None), "hilbert", False) else
                  "tile lists, attention"),
         "attn_ms_per_call": res["attn_ms"],
-        "attn_tflops_nonempty_tiles": res["attn_tile_tflops"],
+        f"attn_tflops_{basis}": res[f"attn_tflops_{basis}"],
         "attn_pct_bf16_peak": res["attn_pct_peak"],
         "perm_gbs": {"gather": res_composed.get("gather_gbs"),
                      "scatter": res_composed.get("scatter_gbs"),
