@@ -174,6 +174,42 @@ def test_attn_fwd_perm_validation(L):
     assert call(vp(0x800000), m=fake_mask(tm=256, tn=64)) == hla.HLA_ERR_UNSUPPORTED
 
 
+def test_attn_fwd_pattern_validation(L):
+    """hla_attn_fwd_pattern checks what hla_attn_fwd and hla_attn_fwd_perm check, the
+    walk, and that the call can walk patches where it is told to; every call here is
+    invalid or unsupported, so nothing is launched."""
+    vp = ctypes.c_void_p
+    q, k, v, o = (vp(0x10000000 * i) for i in range(1, 5))
+
+    def row_major(kind, H, W, p0, p1):
+        m = fake_mask(kind, H, W)
+        m.pat = desc(kind, H, W, p0, p1)
+        return m
+
+    def call(walk=hla.HLA_WALK_PATCHES, order=None, m=None, d=64, dt=hla.HLA_BF16, scale=0.125, B=1, heads=1):
+        m = m or fake_mask()
+        return L.hla_attn_fwd_pattern(q, k, v, order, ctypes.byref(m), o, None, B, heads, m.N, d, dt, scale,
+                                      walk, None)
+
+    assert call(walk=3) == hla.HLA_ERR_INVALID_ARG and "walk" in L.hla_last_error().decode()
+    assert call(walk=-1) == hla.HLA_ERR_INVALID_ARG
+    for walk in (hla.HLA_WALK_AUTO, hla.HLA_WALK_LISTS, hla.HLA_WALK_PATCHES):
+        assert call(walk, order=vp(0x800004)) == hla.HLA_ERR_INVALID_ARG
+        assert call(walk, order=vp(0x10000000 + 1024)) == hla.HLA_ERR_INVALID_ARG
+        assert call(walk, d=48) == hla.HLA_ERR_UNSUPPORTED
+        assert call(walk, scale=0.0) == hla.HLA_ERR_INVALID_ARG
+        assert call(walk, order=vp(0x800000), scale=0.0) == hla.HLA_ERR_INVALID_ARG
+        assert call(walk, m=fake_mask(tm=256, tn=64)) == hla.HLA_ERR_UNSUPPORTED
+        m0 = row_major("rowmajor_slide", 64, 64, 4, 4)
+        m0.n_part = 0
+        assert call(walk, m=m0) == hla.HLA_ERR_INVALID_ARG
+    # patches: row-major and bf16 only, 512 key patches per query tile at most
+    assert call(m=fake_mask()) == hla.HLA_ERR_UNSUPPORTED and "patches" in L.hla_last_error().decode()
+    assert call(m=row_major("rowmajor_slide", 64, 64, 4, 4), dt=hla.HLA_F32) == hla.HLA_ERR_UNSUPPORTED
+    assert call(m=row_major("rowmajor_slide", 256, 256, 128, 128)) == hla.HLA_ERR_UNSUPPORTED
+    assert call(m=row_major("rowmajor_neighborhood", 256, 256, 256, 256)) == hla.HLA_ERR_UNSUPPORTED
+
+
 def test_attn_fwd_hilbert_validation(L):
     """The forward that computes its own Hilbert rows and tile lists takes only the
     Hilbert patterns on 2^k x 2^k grids, in bf16; every call here is invalid or
