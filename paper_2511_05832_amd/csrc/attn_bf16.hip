@@ -110,7 +110,7 @@ constexpr int stages() {
 template <int D, int NW, int MODE, int DIM>
 constexpr int waves_bound() {
   if (MODE == ATTN_RPB) return NW == 4 ? 2 : 1;
-  return stages<D, NW, MODE, DIM>() == 2 ? (NW == 4 ? 4 : MODE == ATTN_PLAIN && DIM == 1 ? 3 : 2) : (NW == 4 ? 3 : 2);
+  return stages<D, NW, MODE, DIM>() == 2 ? (NW == 4 ? 4 : 2) : (NW == 4 ? 3 : 2);
 }
 
 // Combine a value of lane l with lane l ^ 32 (the other half of a query's keys).
@@ -362,11 +362,21 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
   // base, so its offsets are the loop-invariant in-tile ones; the ragged last
   // tile's rows past the end of the sequence read row N - 1, and the mask of that
   // always partial tile drops them.)
+  // At d = 64 copy j's rows are those of copy 0 moved by a multiple of 16, over which
+  // the swizzles repeat, so they too go into the scalar base and two offsets serve
+  // all copies: the two-wave kernel then needs 167 VGPRs (170 and two spilled for
+  // three waves per SIMD, which lost up to 6% in launches of few workgroups; band of
+  // half-width 128 on 64x64, 24 heads, 24.1 -> 22.7 us). At d = 32 registers are
+  // plenty and the scalar additions cost 1.5%.
+  constexpr bool SBASE = MODE == ATTN_PLAIN && D == 64;
+  constexpr int RPC = NT / CPR;   // tile rows per copy of all threads
+  static_assert(RPC % 16 == 0, "the swizzles repeat every 16 rows");
   uint32_t kin[CPW], vin[CPW];
 #pragma unroll
   for (int j = 0; j < CPW; ++j) {
-    kin[j] = (uint32_t)(krow[j] * D + kch[j]) * 2u;
-    vin[j] = (uint32_t)(krow[j] * D + vch[j]) * 2u;
+    const int rj = SBASE ? krow[0] : krow[j];
+    kin[j] = (uint32_t)(rj * D + (SBASE ? kch[0] : kch[j])) * 2u;
+    vin[j] = (uint32_t)(rj * D + (SBASE ? vch[0] : vch[j])) * 2u;
   }
   // HIL: key tile t is the curve's block t, and a copy's tile row is its
   // position in the block. Blocks entered in different states are transposes
@@ -436,6 +446,15 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
       if (k0 + BN <= a.N) {
         Kt += (int64_t)k0 * D;
         Vt += (int64_t)k0 * D;
+        if constexpr (SBASE) {
+#pragma unroll
+          for (int j = 0; j < CPW; ++j)
+            lds_dma16_at(Kt + j * RPC * D, kin[0], lds_addr(base + (j * NW + wave) * 1024));
+#pragma unroll
+          for (int j = 0; j < CPW; ++j)
+            lds_dma16_at(Vt + j * RPC * D, vin[0], lds_addr(base + TILE + (j * NW + wave) * 1024));
+          return;
+        }
 #pragma unroll
         for (int j = 0; j < CPW; ++j) {
           ko[j] = kin[j];
