@@ -97,20 +97,23 @@ constexpr float kFastBound = 4294967296.f;
 // (at most 128 VGPRs). Four waves per SIMD measured, against three at three
 // stages: 256x256 band 185 -> 178 us, 56x56 neighbourhoods 26.1 -> 24.0, 1024-token
 // windows on 160x160 73 -> 68; by patches (three registers spilled) 33x33 on
-// 256x256 303 -> 290; in two-wave workgroups (64-row tiles) 66 -> 60 and 103 -> 91,
-// though a launch too small for the CUs lost 3%. The row-major list kernel needs
-// 150 VGPRs, the one-launch stream copies its Q tiles through the ring and the
-// position bias needs its indices early: they keep three.
+// 256x256 303 -> 290; in two-wave workgroups (64-row tiles) 66 -> 60 and 103 -> 91.
+// Two are no slower in launches of few workgroups either (8 heads on 64x64, window
+// 1024: 18.3 -> 17.2), but for two-wave workgroups at six per CU, of which five fit
+// two stages (24 heads: 44.7 -> 47.6; DIM 4 keeps three there). The row-major list
+// kernel needs 150 VGPRs, the one-launch stream copies its Q tiles through the ring
+// and the position bias needs its indices early: they keep three.
 constexpr int kStages = 3;
 template <int D, int NW, int MODE, int DIM>
 constexpr int stages() {
-  return (MODE == ATTN_PLAIN || MODE == ATTN_GATHER) && D == 64 && DIM != 2 ? 2 : kStages;
+  if (MODE != ATTN_PLAIN && MODE != ATTN_GATHER) return kStages;
+  return DIM == 4 ? (D == 64 && NW == 2 ? 3 : 2) : D == 64 && DIM != 2 ? 2 : kStages;
 }
 // Waves per SIMD the launch bound asks for: what the registers and LDS allow.
 template <int D, int NW, int MODE, int DIM>
 constexpr int waves_bound() {
   if (MODE == ATTN_RPB) return NW == 4 ? 2 : 1;
-  return stages<D, NW, MODE, DIM>() == 2 ? (NW == 4 ? 4 : 2) : (NW == 4 ? 3 : 2);
+  return NW == 2 ? 2 : stages<D, NW, MODE, DIM>() == 2 && DIM != 4 ? 4 : 3;
 }
 
 // Combine a value of lane l with lane l ^ 32 (the other half of a query's keys).
@@ -193,7 +196,8 @@ __device__ __forceinline__ int swz_q(int r) {
 // pattern allows a fraction (33 x 33 cells on 256 x 256: 96 tiles per 128 queries,
 // 16% of their pairs allowed); those of a patch overlap in both directions (30
 // tiles, 53%). The sums run over the same allowed pairs in another order.
-// Measured: 33 x 33 on 256 x 256, d = 64, 8 heads 983 -> 304 us; 16 x 16 windows on
+// DIM 4 is DIM 1 for launches of few workgroups (see few_waves), the same bits.
+// Patches measured: 33 x 33 on 256 x 256, d = 64, 8 heads 983 -> 304 us; 16 x 16 windows on
 // 128 x 128, 32 heads 354 -> 69 us; 13 x 13 neighbourhoods on 71 x 93, 8 heads 56 ->
 // 25 us.
 template <int D, int NW, int MODE, int DIM>
@@ -788,93 +792,99 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
     wait_then_barrier<0>();
   }
 
-  // The math of NB 32-key blocks (from block kb0) of the key tile staged at st (list
-  // entry it): S^T, (mask), online softmax and O^T += V^T P^T.
-  auto blocks_math = [&](const char *tile, int it, int kb0, auto nblocks, auto masked) __attribute__((always_inline)) {
+  // S^T of NB 32-key blocks (from block kb0) of the key tile staged at `tile` (list
+  // entry it), independent accumulators interleaved, the RPB bias and the mask: the
+  // blocks' scores, this lane's 16 NB of them.
+  auto block_scores = [&](const char *tile, int it, int kb0, auto nblocks, auto masked,
+                          auto &s) __attribute__((always_inline)) {
     constexpr int NB = decltype(nblocks)::value;
     // (32 rows leave the swizzles unchanged)
     const char *st = tile + kb0 * 32 * D * 2;
-    // S^T for the 32-key blocks (independent accumulators interleaved), the RPB
-    // bias and the mask: the blocks' scores, this lane's 16 NB of them.
-    auto scores = [&](f32x16 (&s)[NB]) {
 #pragma unroll
-      for (int kb = 0; kb < NB; ++kb) s[kb] = f32x16{};
+    for (int kb = 0; kb < NB; ++kb) s[kb] = f32x16{};
 #pragma unroll
-      for (int c = 0; c < NCH; ++c)
+    for (int c = 0; c < NCH; ++c)
 #pragma unroll
-        for (int kb = 0; kb < NB; ++kb) {
-          const bf16x8 kop = *reinterpret_cast<const bf16x8 *>(st + kaddr[c] + kb * 32 * D * 2);
-          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qop[c], s[kb], 0, 0, 0);
-        }
-      // RPB: scores in natural units plus the bias, s = scale * <q, k> + bias,
-      // from the tile's staged window (entry (rq - rk - dr0) * wc + (cq - ck -
-      // dc0)) or, for a tile whose window did not fit, from the table.
-      if constexpr (RPB) {
-        const int32_t *kid = idx_k(it) + 32 * kb0;
-        const int4 pw = *reinterpret_cast<const int4 *>(lds + WINP + (it & 3) * 16);
-        const int32_t w_dr0 = __builtin_amdgcn_readfirstlane(pw.x);
-        const int32_t w_dc0 = __builtin_amdgcn_readfirstlane(pw.y);
-        const int32_t w_wc = __builtin_amdgcn_readfirstlane(pw.z);
-        const int32_t w_n = __builtin_amdgcn_readfirstlane(pw.w);
-        float bias[NB][16];
-        if (w_n != 0) {
-          const float *win = reinterpret_cast<const float *>(lds + WIN + (it & 1) * kWinCap * 4);
-          const int32_t *term = reinterpret_cast<const int32_t *>(lds + WINB + (it & 3) * BN * 4) + 32 * kb0;
-          const int32_t aq = (rq - w_dr0) * w_wc + (cq - w_dc0);
-#pragma unroll
-          for (int kb = 0; kb < NB; ++kb)
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const int4 *tk = reinterpret_cast<const int4 *>(term + kb * 32 + 16 * g + 8 * half);
-              const int4 lo = tk[0], hi = tk[1];
-              const int32_t bk[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-              for (int e = 0; e < 8; ++e) bias[kb][8 * g + e] = win[aq - bk[e]];
-            }
-        } else {
-          // all 32 bias loads first, so that they are in flight together
-          const int32_t Wm1 = P.W - 1;
-#pragma unroll
-          for (int kb = 0; kb < NB; ++kb)
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const int4 *ids = reinterpret_cast<const int4 *>(kid + kb * 32 + 16 * g + 8 * half);
-              const int4 lo = ids[0], hi = ids[1];
-              const int32_t gk[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const int32_t koff = gk[e] + Wm1 * (int32_t)fdiv((uint32_t)gk[e], P.wdiv);
-                bias[kb][8 * g + e] = rpb_h[rpb_base - koff];
-              }
-            }
-        }
+      for (int kb = 0; kb < NB; ++kb) {
+        const bf16x8 kop = *reinterpret_cast<const bf16x8 *>(st + kaddr[c] + kb * 32 * D * 2);
+        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kop, qop[c], s[kb], 0, 0, 0);
+      }
+    // RPB: scores in natural units plus the bias, s = scale * <q, k> + bias,
+    // from the tile's staged window (entry (rq - rk - dr0) * wc + (cq - ck -
+    // dc0)) or, for a tile whose window did not fit, from the table.
+    if constexpr (RPB) {
+      const int32_t *kid = idx_k(it) + 32 * kb0;
+      const int4 pw = *reinterpret_cast<const int4 *>(lds + WINP + (it & 3) * 16);
+      const int32_t w_dr0 = __builtin_amdgcn_readfirstlane(pw.x);
+      const int32_t w_dc0 = __builtin_amdgcn_readfirstlane(pw.y);
+      const int32_t w_wc = __builtin_amdgcn_readfirstlane(pw.z);
+      const int32_t w_n = __builtin_amdgcn_readfirstlane(pw.w);
+      float bias[NB][16];
+      if (w_n != 0) {
+        const float *win = reinterpret_cast<const float *>(lds + WIN + (it & 1) * kWinCap * 4);
+        const int32_t *term = reinterpret_cast<const int32_t *>(lds + WINB + (it & 3) * BN * 4) + 32 * kb0;
+        const int32_t aq = (rq - w_dr0) * w_wc + (cq - w_dc0);
 #pragma unroll
         for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) s[kb][v] = __builtin_fmaf(s[kb][v], a.scale, bias[kb][v]);
-      }
-      if constexpr (decltype(masked)::value && PATCH) {
-        // slots 8 g .. 8 g + 7 of a block are one row of the patch
-        const uint32_t ent = patch_of(it);
-        const int kr = (int)(ent >> 16) * 8 + 4 * kb0 + half, kc = (int)(ent & 0xffffu) * 8;
-        const uint32_t rspan = (uint32_t)(R.hi - R.lo), cspan = (uint32_t)(R.chi - R.clo);
+          for (int g = 0; g < 2; ++g) {
+            const int4 *tk = reinterpret_cast<const int4 *>(term + kb * 32 + 16 * g + 8 * half);
+            const int4 lo = tk[0], hi = tk[1];
+            const int32_t bk[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const bool cok = (uint32_t)(kc + t - R.clo) <= cspan;
+            for (int e = 0; e < 8; ++e) bias[kb][8 * g + e] = win[aq - bk[e]];
+          }
+      } else {
+        // all 32 bias loads first, so that they are in flight together
+        const int32_t Wm1 = P.W - 1;
 #pragma unroll
-          for (int kb = 0; kb < NB; ++kb)
+        for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const bool ok = cok & ((uint32_t)(kr + 4 * kb + 2 * g - R.lo) <= rspan);
-              s[kb][8 * g + t] = ok ? s[kb][8 * g + t] : -__builtin_inff();
+          for (int g = 0; g < 2; ++g) {
+            const int4 *ids = reinterpret_cast<const int4 *>(kid + kb * 32 + 16 * g + 8 * half);
+            const int4 lo = ids[0], hi = ids[1];
+            const int32_t gk[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int32_t koff = gk[e] + Wm1 * (int32_t)fdiv((uint32_t)gk[e], P.wdiv);
+              bias[kb][8 * g + e] = rpb_h[rpb_base - koff];
             }
-        }
-      } else if constexpr (decltype(masked)::value) mask_blocks<NB, DIM>(s, R, P, tile_of(it) * BN + 32 * kb0 + 8 * half);
-    };
+          }
+      }
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[kb][v] = __builtin_fmaf(s[kb][v], a.scale, bias[kb][v]);
+    }
+    if constexpr (decltype(masked)::value && PATCH) {
+      // slots 8 g .. 8 g + 7 of a block are one row of the patch
+      const uint32_t ent = patch_of(it);
+      const int kr = (int)(ent >> 16) * 8 + 4 * kb0 + half, kc = (int)(ent & 0xffffu) * 8;
+      const uint32_t rspan = (uint32_t)(R.hi - R.lo), cspan = (uint32_t)(R.chi - R.clo);
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const bool cok = (uint32_t)(kc + t - R.clo) <= cspan;
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+          for (int g = 0; g < 2; ++g) {
+            const bool ok = cok & ((uint32_t)(kr + 4 * kb + 2 * g - R.lo) <= rspan);
+            s[kb][8 * g + t] = ok ? s[kb][8 * g + t] : -__builtin_inff();
+          }
+      }
+    } else if constexpr (decltype(masked)::value) {
+      mask_blocks<NB, DIM == 4 ? 1 : DIM>(s, R, P, tile_of(it) * BN + 32 * kb0 + 8 * half);
+    }
+  };
+  // From the scores s of those blocks: online softmax and O^T += V^T P^T.
+  auto block_softmax_pv = [&](const char *tile, int it, int kb0, auto nblocks, auto masked,
+                              auto &s) __attribute__((always_inline)) {
+    constexpr int NB = decltype(nblocks)::value;
+    const char *st = tile + kb0 * 32 * D * 2;
     // Weights p = 2^(s * smul - m) in place of the scores; returns l0 plus this
     // lane's sum of them (one running sum per key block, the first seeded with
     // l0).
-    auto weights = [&](f32x16 (&s)[NB], float m, float l0) {
+    auto weights = [&](float m, float l0) {
       float ls[NB];
 #pragma unroll
       for (int kb = 0; kb < NB; ++kb) ls[kb] = kb == 0 ? l0 : 0.f;
@@ -900,18 +910,16 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
     // l_run being untouched until the tile is accepted. (Straight-line code
     // rather than a retry loop: with a loop, the compiler kept O in two register
     // sets and copied it on every tile.)
-    f32x16 s[NB];
-    scores(s);
     bool slow = !primed;
     float ln = 0.f;
     if (primed) {
-      ln = weights(s, m_run, l_run);
+      ln = weights(m_run, l_run);
       if (__ballot(!(ln <= kFastBound))) {
         slow = true;
         // (the memory clobber makes the K operand reads happen again instead of
         // keeping the first ones in registers across the weights)
         asm volatile("" ::: "memory");
-        scores(s);
+        block_scores(tile, it, kb0, nblocks, masked, s);
       }
     }
     if (slow) {
@@ -944,7 +952,7 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
         }
         m_run = m_new;
       }
-      ln = weights(s, m_run == -__builtin_inff() ? 0.f : m_run, l_run);
+      ln = weights(m_run == -__builtin_inff() ? 0.f : m_run, l_run);
       primed = !__ballot(m_run == -__builtin_inff());
     }
     l_run = ln;
@@ -967,6 +975,12 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
       }
   };
 
+  auto blocks_math = [&](const char *tile, int it, int kb0, auto nblocks, auto masked) __attribute__((always_inline)) {
+    f32x16 s[decltype(nblocks)::value];
+    block_scores(tile, it, kb0, nblocks, masked, s);
+    block_softmax_pv(tile, it, kb0, nblocks, masked, s);
+  };
+
   // A full tile's two blocks together. DIM 1: a partial tile's one after the other,
   // those without an allowed key for any query of the wave left out (their weights
   // would be exact zeros; a band or window edge leaves a wave about half of a
@@ -976,7 +990,14 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
   // too few waves to hide a single block's latencies (1-3% slower), nor with DIM 2:
   // a partial tile of a row-major pattern mostly needs both, and looking cost up to
   // 15%.
+  // DIM 4, where a SIMD has one wave or none to hide latencies with: both blocks'
+  // scores at once and no look at what could be left out, then each block's softmax and
+  // product as with DIM 1, so that finite inputs give the same bits (a key or value that
+  // is not finite reaches every row of its tile, not of its block). 4 heads, against
+  // DIM 1 and both blocks' softmax as one: 49-token windows on 40x40, d = 32 8.5, 7.5
+  // and 7.5 us, d = 64 9.6, 8.5 and 8.7; half-width 40 on 32x32, d = 64 9.6, 8.7, 8.7.
   constexpr bool SPLIT = DIM == 1 && !(D == 64 && NW == 2);
+  constexpr bool PAIR = DIM == 4 && !(D == 64 && NW == 2);
   auto tile_math = [&](const char *st, int it, auto masked) {
     if constexpr (decltype(masked)::value && SPLIT) {
       const int k0 = tile_of(it) * BN;
@@ -984,6 +1005,12 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
       for (int kb = 0; kb < 2; ++kb)
         if (__ballot(region_meets(R, P, k0 + 32 * kb, 32)))
           blocks_math(st, it, kb, std::integral_constant<int, 1>{}, masked);
+    } else if constexpr (decltype(masked)::value && PAIR) {
+      f32x16 s[2];
+      block_scores(st, it, 0, std::integral_constant<int, 2>{}, masked, s);
+      f32x16 s0[1] = {s[0]}, s1[1] = {s[1]};
+      block_softmax_pv(st, it, 0, std::integral_constant<int, 1>{}, masked, s0);
+      block_softmax_pv(st, it, 1, std::integral_constant<int, 1>{}, masked, s1);
     } else {
       if constexpr (decltype(masked)::value && PATCH) {
         // (no allowed key in the patch for any query of the wave)
@@ -1318,6 +1345,22 @@ bool walks_patches(const AttnArgs &a, int BM, hipStream_t s) {
   return st == hipStreamCaptureStatusNone;
 }
 
+// Whether a 1-D pattern takes the kernels for launches of few workgroups (DIM 4): at
+// most one wave per SIMD, and a half for the one-launch kernel at d = 32 (4 heads of
+// half-width 40 on 32x32 10.2 -> 9.5 us; at 256 workgroups of four waves it was 2%
+// slower, and at d = 64, five registers spilled, as fast). Counted by slices and query
+// tiles. Launches just past the line, 384 workgroups of four waves, are 1-4% faster
+// with DIM 1. The two-wave plain kernel at d = 64 takes it, for its three ring stages,
+// at six workgroups per CU.
+template <int D, int NW>
+bool few_waves(const AttnArgs &a) {
+  if (!pattern_is_1d(a.pat.kind) || a.mode == ATTN_RPB) return false;
+  const int64_t wgs = (int64_t)a.BH * a.n_qtiles, cus = device_cu_count();
+  if (D == 64 && NW == 2) return a.mode == ATTN_PLAIN && wgs > 5 * cus && wgs <= 6 * cus;
+  if (a.mode == ATTN_HILBERT) return D == 32 && wgs * NW <= 2 * cus;
+  return wgs * NW <= 4 * cus;
+}
+
 template <int D, int NW>
 hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
   AttnArgs a = a_in;
@@ -1357,8 +1400,18 @@ hipError_t launch(const AttnArgs &a_in, hipStream_t s) {
     else
       hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_PLAIN, DIM>), grid, wg, 0, s, a);
   };
+  const bool few = few_waves<D, NW>(a);
+  if constexpr (D == 32)
+    if (a.mode == ATTN_HILBERT && few) {
+      hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_HILBERT, 4>), grid, wg, 0, s, a);
+      return hipGetLastError();
+    }
   if (a.mode == ATTN_HILBERT)
     hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_HILBERT, 1>), grid, wg, 0, s, a);
+  else if (few && a.mode == ATTN_PLAIN)
+    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_PLAIN, 4>), grid, wg, 0, s, a);
+  else if (few && !(D == 64 && NW == 2))
+    hipLaunchKernelGGL((attn_fwd_bf16<D, NW, ATTN_GATHER, D == 64 && NW == 2 ? 1 : 4>), grid, wg, 0, s, a);
   else if (pattern_is_1d(a.pat.kind))
     run(std::integral_constant<int, 1>{});
   else
