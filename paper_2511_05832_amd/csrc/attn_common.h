@@ -340,14 +340,9 @@ __device__ __forceinline__ void lds_dma16(const void *src, uint32_t dst) {
 // taking two vector instructions per copy. The offset must stay below 2^31.
 __device__ __forceinline__ void lds_dma16_at(const void *base, uint32_t off, uint32_t dst) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  // (the base read back as scalars: the compiler does not always prove it uniform)
-  const uint64_t b = (uint64_t)(uintptr_t)base;
-  const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-  const uint32_t bhi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-  const uint64_t sb = (uint64_t)bhi << 32 | blo;
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
-               : "v"(off), "s"(sb), "s"(__builtin_amdgcn_readfirstlane(dst))
+               : "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(dst))
                : "memory", "m0");
 #endif
 }
