@@ -1284,29 +1284,41 @@ bool patches_fit(const AttnArgs &a, int BM) {
 // On widths that are no multiple of 8 the lists' mask costs more (0.76 ran 1.35x
 // faster by patches, 15x15 on 29x34, and 0.46 0.93x, 21x21 on 20x20): there
 // patches may take 1.4 times the tiles.
+// Where the totals are within a quarter of each other and the fullest query patch has
+// over 1.2 times the tiles of the fullest listed query tile, the lists stay: they share
+// the work more evenly, which decides while every workgroup runs at once (13x13 on
+// 32x32, 64-row tiles, 32 heads 15.6 us by lists, 19.0 by patches; 128 heads of d = 64
+// gave 5% up). Over 2132 measured calls (90 patterns, 8192 to 262144 rows) patches then
+// lose 3% or more to the lists in 58, 18% at the most; 99 and 30% without this. The
+// choice does not look at the number of slices, so a slice's bits do not depend on it.
 bool fewer_by_patches(const AttnArgs &a, int BM) {
   if (!patches_fit(a, BM)) return false;
   const PatternArgs &P = a.pat;
   const int64_t qc = BM / kPatchRows;
   const int64_t nr = (P.H + kPatchRows - 1) / kPatchRows, nc = (P.W + qc - 1) / qc;
-  // Patches along an axis under a query tile of `step` cells: mean of 16 places.
-  auto along = [&](int64_t step, int64_t n, int64_t p, int64_t extent) {
+  // Patches along an axis under a query tile of `step` cells: mean and most of 16
+  // places.
+  auto along = [&](int64_t step, int64_t n, int64_t p, int64_t extent, int64_t &most) {
     const int64_t k = std::min<int64_t>(n, 16);
     int64_t sum = 0;
+    most = 0;
     for (int64_t i = 0; i < k; ++i) {
       const int64_t x = i * n / k * step, y = std::min(extent - 1, x + step - 1);
-      sum += axis_span(P.kind, y, p, extent).hi / 8 - axis_span(P.kind, x, p, extent).lo / 8 + 1;
+      const int64_t c = axis_span(P.kind, y, p, extent).hi / 8 - axis_span(P.kind, x, p, extent).lo / 8 + 1;
+      sum += c;
+      most = std::max(most, c);
     }
     return (double)sum / k;
   };
-  const double per_r = along(kPatchRows, nr, P.p0, P.H), per_c = along(qc, nc, P.p1, P.W);
+  int64_t most_r, most_c;
+  const double per_r = along(kPatchRows, nr, P.p0, P.H, most_r), per_c = along(qc, nc, P.p1, P.W, most_c);
   // Key tiles listed for a query tile: the tiles of 64 positions that the key
   // rows' column ranges touch (all columns when the query tile ends in another
   // grid row than it starts in). The rows' cuts into tiles repeat every `period` rows.
   int64_t period = 1;
   while ((period * P.W) % BN) period *= 2;
   const int64_t k = std::min<int64_t>(a.n_qtiles, 8);
-  double listed = 0;
+  int64_t listed = 0, most_listed = 0;
   for (int64_t i = 0; i < k; ++i) {
     const int32_t x = (int32_t)(i * a.n_qtiles / k * BM), y = std::min(P.N - 1, x + BM - 1);
     const int32_t rx = x / P.W, ry = y / P.W;
@@ -1317,7 +1329,7 @@ bool fewer_by_patches(const AttnArgs &a, int BM) {
     const int64_t r = r1 - r0, left = r & (period - 1);
     uint64_t pos = (uint64_t)r0 * P.W;
     int64_t last = (int64_t)((pos + c1) / BN), tiles = 0, tail = 0;
-    listed += last - (int64_t)((pos + c0) / BN) + 1;
+    const int64_t first = last - (int64_t)((pos + c0) / BN) + 1;
     for (int64_t e = 0; e < std::min(r, period); ++e) {
       pos += P.W;
       const int64_t t0 = (int64_t)((pos + c0) / BN), t1 = (int64_t)((pos + c1) / BN);
@@ -1325,10 +1337,13 @@ bool fewer_by_patches(const AttnArgs &a, int BM) {
       last = t1;
       if (e + 1 == left) tail = tiles;
     }
-    listed += tiles * (r / period) + tail;
+    const int64_t all = first + tiles * (r / period) + tail;
+    listed += all;
+    most_listed = std::max(most_listed, all);
   }
-  const double lists = listed / k * a.n_qtiles;
-  return per_r * nr * per_c * nc < lists * (P.W % 8 ? 1.4 : 1.0);
+  const double weight = P.W % 8 ? 1.4 : 1.0;   // of a listed tile
+  const double lists = weight * listed / k * a.n_qtiles, patches = per_r * nr * per_c * nc;
+  return patches < lists && (most_r * most_c <= 1.2 * weight * most_listed || 1.25 * patches < lists);
 }
 
 // The walk of a call that leaves it to the library. While a stream is captured it is

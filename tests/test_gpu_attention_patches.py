@@ -73,3 +73,20 @@ def test_patches(pat, d, tm):
     # and a mask whose lists a caller has taken walks the lists
     again, again_lse = hla.attn_fwd(*dev, mask, scale)
     assert torch.equal(again, out_l) and torch.equal(again_lse, lse_l)
+
+
+@pytest.mark.parametrize("pat,tm,patches", [
+    (Pat("rowmajor_slide", 48, 56, 12, 12), 64, True), (Pat("rowmajor_window", 32, 64, 8, 8), 128, True),
+    (Pat("rowmajor_neighborhood", 71, 33, 13, 13), 64, True),
+    # fewer tiles by patches, but the fullest patch has 9 against 7
+    (Pat("rowmajor_neighborhood", 32, 32, 13, 13), 64, False),
+    (Pat("rowmajor_slide", 64, 64, 3, 3), 64, False)], ids=str)
+def test_the_choice_of_walk(pat, tm, patches):
+    """Which walk a call takes, the same for 2 slices and for 96 of them."""
+    N, d = pat.N, 32
+    q, k, v = (t.cuda() for t in W.attn_inputs(1, 96, N, d, "bf16", seed=N))
+    mask = hla.build_block_mask(pat, tm, 64)
+    auto = [hla.attn_fwd(*(t[:, :heads].contiguous() for t in (q, k, v)), mask)[0] for heads in (2, 96)]
+    walks = [forward(walk, q, k, v, None, mask, d ** -0.5)[0] for walk in (hla.HLA_WALK_LISTS, hla.HLA_WALK_PATCHES)]
+    assert not torch.equal(*walks)
+    assert torch.equal(auto[1], walks[patches]) and torch.equal(auto[0], auto[1][:, :2])
