@@ -185,8 +185,7 @@ __device__ __forceinline__ int swz_q(int r) {
 // tile's K/V copies; each lane reads its 32 keys' ids from there and loads the
 // 32 bias values (ordinary loads: the compiler waits for them - and, the vmcnt
 // counter being in order, for the copies issued before them - before the
-// softmax, so this mode issues each tile's copies at the end of the step two
-// tiles earlier rather than at its start).
+// softmax, so a step that does so issues its copies at its end).
 //
 // DIM: the patterns the kernel is compiled for, 1 the 1-D (Hilbert) ones, 2 the
 // row-major ones over the tile lists, 3 (PATCH) the row-major ones over patches of
@@ -834,11 +833,10 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
             const int32_t bk[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) bias[kb][8 * g + e] = win[aq - bk[e]];
-            // (in groups of eight reads: left alone the compiler forms all 32 addresses
-            // first. 64x64 band of half-width 128, 8 heads 18.8 -> 18.5 us at d = 64;
-            // 128x128 window, 32 heads 77 -> 69 at d = 32, which then takes four waves
-            // per SIMD. Two-wave workgroups are left to it: 1% slower in groups.)
-            if constexpr (NW == 4) __builtin_amdgcn_sched_barrier(0);
+            // (at d = 32 in groups of eight reads: left alone the compiler forms all 32
+            // addresses first. 124 registers instead of 133 then let four waves per SIMD
+            // in: 128x128 window, 32 heads 83 -> 76 us. The others gain nothing from it.)
+            if constexpr (NW == 4 && D == 32) __builtin_amdgcn_sched_barrier(0);
           }
       } else {
         // all 32 bias loads first, so that they are in flight together
@@ -1062,21 +1060,29 @@ __global__ void __launch_bounds__(64 * NW, (waves_bound<D, NW, MODE, DIM>()))
     if constexpr (GATHER) {
       if (it + 3 < ntot) issue_idx(it + 3);
     }
-    if constexpr (!RPB) {
+    // RPB: entry it + 1's window (its indices arrived with the wait above), then
+    // the ring refill, then entry it + 3's indices (slot (it + 3) % 4 last held
+    // entry it - 1's). At d = 64 with DIM 1 and four waves they go out now, so that the
+    // window has this step's products to arrive in (128x128 window, 32 heads 120.5 ->
+    // 119.4 us; two waves lost 1-4%, d = 32 nothing either way); else, and in a step
+    // whose bias comes straight from the table, at its end, as the compiler's wait for
+    // the table's loads covers every copy in flight.
+    constexpr bool EARLY = DIM == 1 && NW == 4 && D == 64;
+    const bool late = RPB && (!EARLY || *reinterpret_cast<const int32_t *>(lds + WINP + (it & 3) * 16 + 12) == 0);
+    auto refill = [&] {
+      if constexpr (RPB) {
+        if (it + 1 < ntot && wave == (it + 1) % NW) issue_window(it + 1);
+      }
       if (it + 2 < ntot) issue_tile(it + 2, nstage);
-    }
+      if constexpr (RPB) {
+        if (it + 3 < ntot) issue_idx(it + 3);
+      }
+    };
+    if (!late) refill();
     const char *st = lds + stage * STAGE;
     stage = stage == 2 ? 0 : stage + 1;
     tile_math(st, it, masked);
-    // RPB: at the end of the step, entry it + 1's window (its indices arrived
-    // before this step's barrier), then the ring refill (stage (it + 2) % 3 held
-    // tile it - 1, which every wave finished before this step's barrier), then
-    // entry it + 3's indices (slot (it + 3) % 4 last held entry it - 1's).
-    if constexpr (RPB) {
-      if (it + 1 < ntot && wave == (it + 1) % NW) issue_window(it + 1);
-      if (it + 2 < ntot) issue_tile(it + 2, nstage);
-      if (it + 3 < ntot) issue_idx(it + 3);
-    }
+    if (late) refill();
   };
   // Epilogue: normalise and store the rows straight from the accumulators. Lane
   // (col, half) holds, per d block and 8-row group a, the four values
