@@ -272,15 +272,19 @@ class _RowLists:
     __slots__ = ("n_full", "n_part", "full_idx", "part_idx", "struct", "own")
 
 
-def _handed_out(name):
-    def get(self):
-        self._lists.own = False
-        return getattr(self._lists, name)
+class _HandedOut:
+    """A list of a BlockMask: the first look at it ends its lists' being the builder's
+    own and leaves the tensor on the mask as an ordinary attribute."""
 
-    def set_(self, value):
-        self._lists.own = False
-        setattr(self._lists, name, value)
-    return property(get, set_)
+    def __set_name__(self, owner, name):
+        self.name = name
+
+    def __get__(self, mask, owner=None):
+        if mask is None:
+            return self
+        mask._lists.own = False
+        value = mask.__dict__[self.name] = getattr(mask._lists, self.name)
+        return value
 
 
 class BlockMask:
@@ -295,9 +299,17 @@ class BlockMask:
     then finds its tiles from the pattern (hla_attn_fwd_pattern), which can be faster
     and sums the same pairs in another order."""
 
-    n_full, n_part = _handed_out("n_full"), _handed_out("n_part")
-    full_idx, part_idx = _handed_out("full_idx"), _handed_out("part_idx")
-    struct = _handed_out("struct")
+    n_full, n_part, full_idx, part_idx = _HandedOut(), _HandedOut(), _HandedOut(), _HandedOut()
+
+    @property
+    def struct(self) -> BlockMaskStruct:
+        self._lists.own = False
+        return self._lists.struct
+
+    @struct.setter
+    def struct(self, value: BlockMaskStruct):
+        self._lists.own = False
+        self._lists.struct = value
 
     def __init__(self, pattern, tile_m: int, tile_n: int, device="cuda", columns: bool = False,
                  totals: bool = True):
@@ -373,10 +385,19 @@ def build_block_mask(pattern, tile_m: int, tile_n: int, device="cuda",
     return BlockMask(pattern, tile_m, tile_n, device, columns).build()
 
 
+class _OtherLists:
+    """Any object with a ``struct`` in place of a BlockMask."""
+    __slots__ = ("struct",)
+    own = False
+
+    def __init__(self, mask):
+        self.struct = mask.struct
+
+
 def _lists_of(mask):
-    """A mask's C struct, and whether its lists are known to be the builder's own."""
-    lists = getattr(mask, "_lists", None)
-    return (mask.struct, False) if lists is None else (lists.struct, lists.own)
+    """A mask's C struct (.struct), and whether its lists are known to be the builder's
+    own (.own)."""
+    return mask._lists if isinstance(mask, BlockMask) else _OtherLists(mask)
 
 
 def _attn_fwd_args(q, k, v, scale, out, lse, with_lse):
@@ -407,13 +428,13 @@ def attn_fwd(q, k, v, mask: BlockMask, scale: Optional[float] = None,
              with_lse: bool = True):
     """Block-sparse attention forward (hla_attn_fwd). Returns (out, lse or None)."""
     B, Hh, N, d, scale, out, lse = _attn_fwd_args(q, k, v, scale, out, lse, with_lse)
-    struct, own = _lists_of(mask)
-    if own:
-        _check(lib().hla_attn_fwd_pattern(_ptr(q), _ptr(k), _ptr(v), 0, ctypes.byref(struct),
+    lists = _lists_of(mask)
+    if lists.own:
+        _check(lib().hla_attn_fwd_pattern(_ptr(q), _ptr(k), _ptr(v), 0, ctypes.byref(lists.struct),
                                           _ptr(out), _ptr(lse), B, Hh, N, d, _dtype_code(q), scale,
                                           HLA_WALK_AUTO, _stream(q)))
     else:
-        _check(lib().hla_attn_fwd(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(struct), _ptr(out),
+        _check(lib().hla_attn_fwd(_ptr(q), _ptr(k), _ptr(v), ctypes.byref(lists.struct), _ptr(out),
                                   _ptr(lse), B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return out, lse
 
@@ -430,14 +451,14 @@ def attn_fwd_perm(q, k, v, order, mask: BlockMask, scale: Optional[float] = None
     B, Hh, N, d, scale, out, lse = _attn_fwd_args(q, k, v, scale, out, lse, with_lse)
     if order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order has {order.numel()} entries, expected N = {N}")
-    struct, own = _lists_of(mask)
-    if own:
+    lists = _lists_of(mask)
+    if lists.own:
         _check(lib().hla_attn_fwd_pattern(_ptr(q), _ptr(k), _ptr(v), _ptr(order),
-                                          ctypes.byref(struct), _ptr(out), _ptr(lse), B, Hh, N,
+                                          ctypes.byref(lists.struct), _ptr(out), _ptr(lse), B, Hh, N,
                                           d, _dtype_code(q), scale, HLA_WALK_AUTO, _stream(q)))
     else:
         _check(lib().hla_attn_fwd_perm(_ptr(q), _ptr(k), _ptr(v), _ptr(order),
-                                       ctypes.byref(struct), _ptr(out), _ptr(lse), B, Hh, N, d,
+                                       ctypes.byref(lists.struct), _ptr(out), _ptr(lse), B, Hh, N, d,
                                        _dtype_code(q), scale, _stream(q)))
     return out, lse
 
@@ -470,12 +491,12 @@ def attn_fwd_rpb(q, k, v, order, rpb, mask: BlockMask, scale: Optional[float] = 
     _require(rpb, "rpb")
     if order.dtype != torch.int32 or order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order must be int32 with N = {N} entries")
-    pat = _lists_of(mask)[0].pat
+    pat = _lists_of(mask).struct.pat
     H, W = pat.H, pat.W
     if rpb.dtype != torch.float32 or tuple(rpb.shape) != (Hh, 2 * H - 1, 2 * W - 1):
         raise HLAError(HLA_ERR_INVALID_ARG, f"rpb must be float32 [{Hh}, {2 * H - 1}, {2 * W - 1}]")
     _check(lib().hla_attn_fwd_rpb(_ptr(q), _ptr(k), _ptr(v), _ptr(order), _ptr(rpb),
-                                  ctypes.byref(_lists_of(mask)[0]), _ptr(out), _ptr(lse), B, Hh, N, d,
+                                  ctypes.byref(_lists_of(mask).struct), _ptr(out), _ptr(lse), B, Hh, N, d,
                                   _dtype_code(q), scale, _stream(q)))
     return out, lse
 
@@ -512,7 +533,7 @@ def attn_bwd(q, k, v, out, dout, lse, mask: BlockMask, scale: Optional[float] = 
     B, Hh, N, d, scale, dq, dk, dv, stats = _attn_bwd_args(q, k, v, out, dout, lse, scale,
                                                            dq, dk, dv, stats)
     _check(lib().hla_attn_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                              ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(stats),
+                              ctypes.byref(_lists_of(mask).struct), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(stats),
                               B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return dq, dk, dv
 
@@ -529,7 +550,7 @@ def attn_bwd_perm(q, k, v, out, dout, lse, order, mask: BlockMask, scale: Option
     if order.dtype != torch.int32 or order.numel() != N:
         raise HLAError(HLA_ERR_INVALID_ARG, f"order must be int32 with N = {N} entries")
     _check(lib().hla_attn_bwd_perm(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                                   _ptr(order), ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk),
+                                   _ptr(order), ctypes.byref(_lists_of(mask).struct), _ptr(dq), _ptr(dk),
                                    _ptr(dv), _ptr(stats), B, Hh, N, d, _dtype_code(q), scale,
                                    _stream(q)))
     return dq, dk, dv
@@ -554,7 +575,7 @@ def attn_bwd_noalloc(q, k, v, out, dout, lse, mask: BlockMask, scale: Optional[f
     for t, n in ((dq, "dq"), (dk, "dk"), (dv, "dv")):
         _require(t, n)
     _check(lib().hla_attn_bwd_noalloc(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(dout), _ptr(lse),
-                                      ctypes.byref(_lists_of(mask)[0]), _ptr(dq), _ptr(dk), _ptr(dv),
+                                      ctypes.byref(_lists_of(mask).struct), _ptr(dq), _ptr(dk), _ptr(dv),
                                       B, Hh, N, d, _dtype_code(q), scale, _stream(q)))
     return dq, dk, dv
 

@@ -7,6 +7,7 @@ Tolerances as in the attention tests: 2e-2 (bf16) and 1e-4 (f32) absolute for
 outputs of N(0, 1) values, 1e-3 for lse.
 """
 import copy
+import types
 
 import numpy as np
 import pytest
@@ -22,19 +23,25 @@ LISTS = ("n_full", "full_idx", "n_part", "part_idx")
 
 
 def test_lists_are_the_builders_until_taken():
-    """Reading a list or the struct, by any name or copy, ends it; nothing else does."""
+    """Reading a list or the struct, by any name or copy, or another struct ends it;
+    nothing else does. A list is an ordinary attribute after that."""
     pat = Pat("rowmajor_slide", 24, 32, 4, 4)
     for name in LISTS + ("struct",):
         mask = hla.BlockMask(pat, 128, 64, device="cpu", columns=True)
         twin = copy.copy(mask)
         assert mask.N == 0 and mask.n_qtiles == 6 and mask.totals.numel() == 2 and mask.n_full_t.numel() == 12
-        assert hla._lists_of(mask)[1] and hla._lists_of(twin)[1]
-        getattr(twin, name)
-        assert not hla._lists_of(mask)[1]
+        assert hla._lists_of(mask).own and hla._lists_of(twin).own
+        got = getattr(twin, name)
+        assert not hla._lists_of(mask).own
+        assert getattr(twin, name) is got and getattr(mask, name) is got
+        if name != "struct":
+            assert got.data_ptr() == getattr(mask.struct, name)
     mask = hla.BlockMask(pat, 128, 64, device="cpu")
-    mask.n_part = torch.zeros_like(mask._lists.n_part)
-    assert not hla._lists_of(mask)[1]
-    assert not hla._lists_of(hla.BlockMask(Pat("hilbert_slide", 16, 16, 9), 128, 64, device="cpu"))[1]
+    mask.struct = other = hla.BlockMaskStruct()
+    assert not hla._lists_of(mask).own and hla._lists_of(mask).struct is other
+    assert not hla._lists_of(hla.BlockMask(Pat("hilbert_slide", 16, 16, 9), 128, 64, device="cpu")).own
+    plain = types.SimpleNamespace(struct=other)      # any object with a struct will do
+    assert not hla._lists_of(plain).own and hla._lists_of(plain).struct is other
 
 
 def thin(mask, rng):
