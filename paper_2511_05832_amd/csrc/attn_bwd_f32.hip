@@ -44,8 +44,6 @@ namespace {
 
 constexpr int BN = 64;   // keys per key tile, and rows per ring stage
 
-__device__ __forceinline__ int swz(int r) { return (r & 3) | (((r >> 3) & 1) << 2); }
-
 // LDS offsets of this lane's reads of a 32-row block of a swizzled row tile.
 template <int D>
 struct Reads {
@@ -56,7 +54,7 @@ struct Reads {
   __device__ __forceinline__ void init(int col, int half) {
     const int r = row_perm(col);
 #pragma unroll
-    for (int c = 0; c < D / 8; ++c) row[c] = r * ROW + (((half * (D / 8) + c) ^ swz(r)) * 16);
+    for (int c = 0; c < D / 8; ++c) row[c] = r * ROW + (((half * (D / 8) + c) ^ swz_f32(r)) * 16);
     const int e = col * NDB;   // first column
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -110,7 +108,7 @@ __device__ __forceinline__ void copy_rows(const float *X, const float *Y, int p0
 #pragma unroll
   for (int j = 0; j < CPW; ++j) {
     const int p = (j * NW + wave) * 64 + lane;
-    const int r = p / CPR, c = (p % CPR) ^ swz(r);
+    const int r = p / CPR, c = (p % CPR) ^ swz_f32(r);
     const int64_t row = GATHER ? (int64_t)rows[r] : (int64_t)min(p0 + r, N - 1);
     lds_dma16(X + row * D + 4 * c, lds_addr(base + (j * NW + wave) * 1024));
     lds_dma16(Y + row * D + 4 * c, lds_addr(base + TILE + (j * NW + wave) * 1024));

@@ -237,6 +237,9 @@ __device__ __forceinline__ int row_perm(int i) {
 // band of half-width 128: 118.6 -> 110.9 us); at d = 32, with twice the waves
 // per SIMD, it is 2% slower, so there the order is left to the compiler.
 
+// Per-row XOR swizzle of a row tile's 16-byte chunks in LDS.
+__device__ __forceinline__ int swz_f32(int r) { return (r & 3) | (((r >> 3) & 1) << 2); }
+
 // acc = rows . b: A = the block's rows, this lane's row in 16-byte chunks at
 // blk + addr[c]; b the other operand's chunks. NC chunks of four contraction steps,
 // in CHAINS (1, 2 or 4) accumulation chains of equal parts of d, each added to the

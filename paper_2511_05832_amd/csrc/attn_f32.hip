@@ -102,7 +102,6 @@ __global__ void __launch_bounds__(64 * NW * KS, 2) attn_fwd_f32(AttnArgs a) {
   // p / CPR, chunk (p % CPR) ^ swizzle of K and chunk p % CPR of V. Key rows past
   // the end of the sequence read row N - 1 (such a tile is always partial and
   // every allowed region ends at N - 1).
-  auto swz = [](int r) { return (r & 3) | (((r >> 3) & 1) << 2); };
   auto issue_tile = [&](int i, int stage) {
     char *base = lds + stage * STAGE;
     const int k0 = tile_of(i) * BN;
@@ -111,7 +110,7 @@ __global__ void __launch_bounds__(64 * NW * KS, 2) attn_fwd_f32(AttnArgs a) {
       const int p = (j * NWT + wave) * 64 + lane;
       const int r = p / CPR, c = p % CPR;
       const int64_t row = GATHER ? (int64_t)idx_k(i)[r] : (int64_t)min(k0 + r, a.N - 1);
-      lds_dma16(K + row * D + 4 * (c ^ swz(r)), lds_addr(base + (j * NWT + wave) * 1024));
+      lds_dma16(K + row * D + 4 * (c ^ swz_f32(r)), lds_addr(base + (j * NWT + wave) * 1024));
       lds_dma16(V + row * D + 4 * c, lds_addr(base + TILE + (j * NWT + wave) * 1024));
     }
   };
@@ -140,7 +139,7 @@ __global__ void __launch_bounds__(64 * NW * KS, 2) attn_fwd_f32(AttnArgs a) {
 #pragma unroll
   for (int c = 0; c < D / 8; ++c) {
     const int r = row_perm(col);
-    kaddr[c] = r * ROW + (((half * (D / 8) + c) ^ swz(r)) * 16);
+    kaddr[c] = r * ROW + (((half * (D / 8) + c) ^ swz_f32(r)) * 16);
   }
   const int vaddr = TILE + 8 * half * ROW + col * (4 * NDB);
 

@@ -488,7 +488,11 @@ hipError_t launch_tile(const ProjArgs &a, hipStream_t s) {
 }
 
 // Tile shape: the widest feature tile that divides F, in tiles of 128 tokens;
-// 64-token tiles where those would leave CUs without work.
+// 64-token tiles where those would leave CUs without work. One contraction loop
+// serves every K, down to two steps (K = 64). Against a kernel that kept a token
+// block's rows in registers and walked the feature tiles (K = 64 and 128), 16 x 4096
+// tokens: QKV 13.9 -> 7.4 and 24.6 -> 15.6 us, output projection to K features 6.5 ->
+// 4.3 and 11.7 -> 7.0; 1024 tokens 5.5 -> 3.9, 9.7 -> 4.4, 4.0 -> 2.8, 5.0 -> 3.9.
 template <int MODE>
 hipError_t launch_tile_any(const ProjArgs &p, hipStream_t s) {
   const int cus = device_cu_count();
