@@ -15,6 +15,8 @@
 // against plain FMAs with four lanes per row, which read every K and V element
 // from LDS once per 16 FMAs: band of half-width 128 on 64x64 at d = 64, 8 heads
 // 128 -> 36 us, 32 heads 293 -> 111 us (113 TFLOP/s over the listed tiles).
+// With one wave per SIMD (8 heads there: 256 workgroups) nothing fills its waits:
+// the matrix cores are busy 36% of the time.
 //
 //   S^T = K Q^T     A = K rows from LDS, B = the wave's q in registers. Lane half
 //                   h contracts d in [h D/2, (h+1) D/2), so a lane reads its part
